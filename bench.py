@@ -231,6 +231,21 @@ def summarize_valu(root):
     print(json.dumps(out, indent=1))
 
 
+def swept(p, plan):
+    """`plan` with the rays and ray-intervals that the operator sweeps: the
+    frequencies of a slab whose opacity ratios agree to 1e-12 share one ray
+    (an even profile has half as many rays as frequencies)."""
+    most = 0
+    for op in np.sort(p.opac, axis=1):
+        n, i = 0, 0
+        while i < len(op):
+            i = int(np.searchsorted(op, op[i] * (1 + 1e-12), side="right"))
+            n += 1
+        most = max(most, n)
+    per = (p.n_mu // 2) * most
+    return {**plan, "rays": p.n_atm * per, "intervals": int(np.sum(p.ns - 1)) * per}
+
+
 def op_bytes(p, plan, coef_mode, s):
     """Algorithmic bytes of one operator application with the sweep in a
     coefficient mode (0: (E, w) pairs streamed, 1: w streamed, 2: both
@@ -239,7 +254,7 @@ def op_bytes(p, plan, coef_mode, s):
     for the derived modes, kappa (8) or kappa and 1 / kappa (16), per depth
     point dtau (8, derived modes), and sigma read and sigma_out written
     (FP64, 16 bytes per unknown)."""
-    n_rays = p.n_atm * (p.n_mu // 2) * p.n_nu
+    n_rays = plan.get("rays", p.n_atm * (p.n_mu // 2) * p.n_nu)
     coef = {0: 2 * s, 1: s, 2: 0}[coef_mode] * plan["intervals"]
     ray = {0: 8, 1: 16, 2: 24}[coef_mode] * n_rays
     dep = 0 if coef_mode == 0 else 8 * int(np.sum(p.ns))
@@ -569,7 +584,7 @@ def main():
     y = torch.empty_like(v)
     with B.setup(p, rtol=RTOL, restart=30, maxit=20000, precision=B.RT_PREC_MIXED,
                  autotune=True) as h:
-        plan = h.plan_info()
+        plan = swept(p, h.plan_info())
         cfg32, cfg64 = h.sweep_config(True), h.sweep_config(False)
         o = h.effective_options()
         out["launch_plan"] = {"mixed": dict(chunk=plan["chunk"], sweep_waves=cfg32["waves"],

@@ -324,6 +324,55 @@ int check_tile_range(const std::vector<int> &ns, int L, int n_nu) {
     return RT_OK;
 }
 
+// Frequencies of a slab whose opacity ratios agree to kSameOpac share a formal
+// solution: under complete redistribution the source does not depend on
+// frequency and a ray sees it only through kappa = r_p / |mu|, so their
+// weights w_p phi_p add.  The group's opacity is the weighted mean, which
+// cancels the first-order difference; the second is below 1e-24.  A line
+// profile that is even about its centre halves the rays this way (the two
+// halves of a computed grid differ by up to 1.5e-14); without equal opacities
+// every group is one frequency.  512 slabs of 101 frequencies: the FP64
+// operator takes 250 us with a ray per frequency, 140 us with one per opacity.
+// Strongest opacity first; every slab gets the same number of rays (the largest
+// count), the rest with weight zero.
+constexpr double kSameOpac = 1e-12;
+
+int merge_frequencies(const rt_problem *p, std::vector<double> &opac, std::vector<double> &wphi) {
+    const int n = p->n_nu;
+    std::vector<std::pair<double, double>> f(n);  // (opacity, weight)
+    std::vector<double> kap((size_t)p->n_atm * n), w((size_t)p->n_atm * n);
+    std::vector<int> count(p->n_atm, 0);
+    int most = 0;
+    for (int a = 0; a < p->n_atm; ++a) {
+        const double *op = p->opac + (long long)a * n, *ph = p->phi + (long long)a * n;
+        for (int q = 0; q < n; ++q) f[q] = {op[q], p->w_nu[q] * ph[q]};
+        std::sort(f.begin(), f.end());
+        int g = 0;
+        for (int i = 0; i < n; ++g) {
+            const double first = f[i].first;
+            double sw = 0.0, excess = 0.0;  // of the opacity over the first's
+            for (; i < n && f[i].first - first <= kSameOpac * first; ++i) {
+                sw += f[i].second;
+                excess += f[i].second * (f[i].first - first);
+            }
+            kap[(size_t)a * n + g] = sw > 0.0 ? first + excess / sw : first;
+            w[(size_t)a * n + g] = sw;
+        }
+        count[a] = g;
+        most = std::max(most, g);
+    }
+    opac.resize((size_t)p->n_atm * most);
+    wphi.resize((size_t)p->n_atm * most);
+    for (int a = 0; a < p->n_atm; ++a)
+        for (int g = 0; g < most; ++g) {
+            const bool on = g < count[a];
+            const size_t e = (size_t)a * n + (on ? count[a] - 1 - g : 0);
+            opac[(size_t)a * most + g] = kap[e];
+            wphi[(size_t)a * most + g] = on ? w[e] : 0.0;
+        }
+    return most;
+}
+
 template <typename T>
 int dalloc(T **p, size_t count) {
     *p = nullptr;
@@ -501,9 +550,9 @@ int rt_num_unknowns(const rt_handle *h) { return h ? h->n_unk : 0; }
 void rt_destroy(rt_handle *h) {
     if (!h) return;
     void *ptrs[] = {h->d_tau,   h->d_B,     h->d_opac,    h->d_phi,     h->d_mu_pos, h->d_w_pos,
-                    h->d_w_nu,  h->d_pt_atm, h->d_atm,    h->d_blk,     h->d_rayc,   h->d_coef64,
+                    h->d_w_nu,  h->d_wphi,  h->d_pt_atm, h->d_atm,    h->d_blk,     h->d_rayc,   h->d_coef64,
                     h->d_atm_tail, h->d_blk_tail,
-                    h->d_q,     h->d_qt,      h->d_dirc,    h->d_Qs,
+                    h->d_rayc_nu, h->d_opac_c, h->d_wphi_c, h->d_qt,      h->d_dirc,    h->d_Qs,
                     h->d_coef32, h->d_partial, h->d_diag,  h->d_dinv,   h->d_b,
                     h->d_V,     h->d_H,     h->d_cs,      h->d_sn,      h->d_g,      h->d_w,
                     h->d_r,     h->d_rh,    h->d_p,       h->d_v,       h->d_s,      h->d_t,
@@ -588,14 +637,18 @@ int rt_setup(rt_handle **out, const rt_problem *p, const rt_options *o) {
     h->n_unk = 2 * acc;
 
     // ---- plan: chunks, wave-batches, blocks, tiles, partial sums
-    const int rays = h->M * h->n_nu;
+    std::vector<double> opac_c, wphi_c;
+    h->nc = merge_frequencies(p, opac_c, wphi_c);
+    const int rays = h->M * h->nc;
     h->L = opt.chunk ? opt.chunk : auto_chunk(h->ns, rays);
     for (int n : h->ns)
         if ((long long)kWave * h->L < n - 1) {
             delete h;
             return fail(RT_EINVAL, "options.chunk too short for ns (need 64 * chunk >= ns - 1)");
         }
-    if ((rc = check_tile_range(h->ns, h->L, h->n_nu)) != RT_OK) {
+    // the same test as rt_validate, which does not look for equal opacities
+    if ((rc = check_tile_range(h->ns, opt.chunk ? opt.chunk : auto_chunk(h->ns, h->M * h->n_nu),
+                               h->n_nu)) != RT_OK) {
         delete h;
         return rc;
     }
@@ -615,12 +668,12 @@ int rt_setup(rt_handle **out, const rt_problem *p, const rt_options *o) {
         AtmDesc d{};
         d.ns = h->ns[a];
         d.doff = h->doff[a];
-        const SlabTiles t = slab_tiles(d.ns, h->L, h->n_nu);
+        const SlabTiles t = slab_tiles(d.ns, h->L, h->nc);
         d.C = t.C;
         d.Leff = t.Leff;
         d.nlong = t.nlong;
         d.G = t.G;
-        d.n_nu = h->n_nu;
+        d.n_nu = h->nc;
         d.nwb = t.nwb;
         d.bstride = t.bstride;
         d.ray_off = a * rays;
@@ -745,7 +798,9 @@ int rt_setup(rt_handle **out, const rt_problem *p, const rt_options *o) {
         std::fill(pt_atm.begin() + h->doff[a], pt_atm.begin() + h->doff[a] + h->ns[a], a);
     std::vector<double> B(acc, 1.0);
     if (p->B) std::copy(p->B, p->B + acc, B.begin());
-    const size_t nphi = (size_t)h->n_atm * h->n_nu;
+    const size_t nphi = (size_t)h->n_atm * h->n_nu, nmerged = (size_t)h->n_atm * h->nc;
+    std::vector<double> wphi(nphi);  // spectral weights w_p phi_p of every frequency
+    for (size_t e = 0; e < nphi; ++e) wphi[e] = p->w_nu[e % h->n_nu] * p->phi[e];
 #define RT_TRY(x)            \
     do {                     \
         int _rc = (x);       \
@@ -763,11 +818,14 @@ int rt_setup(rt_handle **out, const rt_problem *p, const rt_options *o) {
     RT_TRY(dalloc(&h->d_fsig, (size_t)2 * acc));
     RT_TRY(dalloc(&h->d_w_pos, h->M));
     RT_TRY(dalloc(&h->d_w_nu, h->n_nu));
+    RT_TRY(dalloc(&h->d_wphi, nphi));
+    RT_TRY(dalloc(&h->d_opac_c, nmerged));
+    RT_TRY(dalloc(&h->d_wphi_c, nmerged));
     RT_TRY(dalloc(&h->d_pt_atm, acc));
     RT_TRY(dalloc(&h->d_atm, h->n_atm));
     RT_TRY(dalloc(&h->d_blk, h->n_blocks));
     RT_TRY(dalloc(&h->d_rayc, (size_t)h->n_atm * rays));
-    RT_TRY(dalloc(&h->d_q, (size_t)h->n_atm * rays));
+    RT_TRY(dalloc(&h->d_rayc_nu, nphi * h->M));
     RT_TRY(dalloc(&h->d_qt, (size_t)h->n_qt));
     RT_TRY(dalloc(&h->d_dirc, (size_t)h->M));
     RT_TRY(dalloc(&h->d_Qs, (size_t)h->n_atm));
@@ -801,6 +859,9 @@ int rt_setup(rt_handle **out, const rt_problem *p, const rt_options *o) {
     RT_TRY(h2d(h->d_mu_idx, mu_index.data(), (size_t)2 * h->M));
     RT_TRY(h2d(h->d_w_pos, w_pos.data(), h->M));
     RT_TRY(h2d(h->d_w_nu, p->w_nu, h->n_nu));
+    RT_TRY(h2d(h->d_wphi, wphi.data(), nphi));
+    RT_TRY(h2d(h->d_opac_c, opac_c.data(), nmerged));
+    RT_TRY(h2d(h->d_wphi_c, wphi_c.data(), nmerged));
     RT_TRY(h2d(h->d_pt_atm, pt_atm.data(), acc));
     RT_TRY(h2d(h->d_atm, h->atm_h.data(), h->n_atm));
     RT_TRY(h2d(h->d_blk, h->blk_h.data(), h->n_blocks));
@@ -813,16 +874,18 @@ int rt_setup(rt_handle **out, const rt_problem *p, const rt_options *o) {
 
     // ---- precompute: ray constants, tile coefficients, D and D^-1, b
     hipStream_t s = nullptr;
-    RT_TRY(hip_check(launch_ray_setup(h->n_atm, h->d_atm, h->d_mu_pos, h->d_w_pos, h->M,
-                                      h->d_w_nu, h->d_phi, h->n_nu, h->normalize, h->d_rayc,
-                                      h->d_q, h->d_dirc, h->d_Qs, s),
+    RT_TRY(hip_check(launch_ray_setup(h->n_atm, h->d_mu_pos, h->d_w_pos, h->M, h->d_wphi,
+                                      h->n_nu, h->normalize, h->d_rayc_nu, h->d_dirc, h->d_Qs, s),
                      "ray setup launch"));
-    RT_TRY(hip_check(launch_coef_build(h->n_blocks, h->W, h->d_atm, h->d_blk, h->d_tau, h->d_opac,
-                                       h->d_mu_pos, h->fs, h->d_q, h->d_coef64, h->d_coef32,
-                                       h->d_w64, h->d_w32, h->d_qt, h->d_kt, s),
+    RT_TRY(hip_check(launch_ray_setup(h->n_atm, h->d_mu_pos, h->d_w_pos, h->M, h->d_wphi_c, h->nc,
+                                      h->normalize, h->d_rayc, h->d_dirc, h->d_Qs, s),
+                     "ray setup launch"));
+    RT_TRY(hip_check(launch_coef_build(h->n_blocks, h->W, h->d_atm, h->d_blk, h->d_tau,
+                                       h->d_opac_c, h->d_mu_pos, h->fs, h->d_rayc, h->d_coef64,
+                                       h->d_coef32, h->d_w64, h->d_w32, h->d_qt, h->d_kt, s),
                      "coefficient launch"));
-    RT_TRY(hip_check(launch_diag(acc, h->d_pt_atm, h->d_atm, h->d_tau, h->d_opac, h->d_mu_pos,
-                                 h->d_rayc, h->M, h->n_nu, h->fs, h->d_diag, h->d_dinv, s),
+    RT_TRY(hip_check(launch_diag(acc, h->d_pt_atm, h->d_atm, h->d_tau, h->d_opac_c, h->d_mu_pos,
+                                 h->d_rayc, h->M, h->nc, h->fs, h->d_diag, h->d_dinv, s),
                      "diagonal launch"));
     RT_TRY(hip_check(apply_operator(h, nullptr, nullptr, h->d_b, nullptr, false, 1, s),
                      "right-hand side launch"));

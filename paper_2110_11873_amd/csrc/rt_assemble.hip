@@ -330,11 +330,11 @@ int plan_assembly(rt_handle *h, hipStream_t s) {
     long long best_waste = 0;
     for (const AsmVariant &v : kVariants) {
         const int maxw = v.nt / kWave;
-        const int cpm = (h->n_nu + v.rg - 1) / v.rg;
+        const int cpm = (h->nc + v.rg - 1) / v.rg;
         const int chunks = h->M * cpm;
         const int slices = (chunks + maxw - 1) / maxw;
         const int nw = (chunks + slices - 1) / slices;
-        const long long waste = (long long)slices * nw * v.rg - (long long)h->M * h->n_nu;
+        const long long waste = (long long)slices * nw * v.rg - (long long)h->M * h->nc;
         if (!best_rg || slices < best_slices || (slices == best_slices && waste < best_waste)) {
             best_rg = v.rg;
             best_slices = slices;
@@ -343,7 +343,7 @@ int plan_assembly(rt_handle *h, hipStream_t s) {
         }
     }
     h->asm_rg = best_rg;
-    h->asm_cpm = (h->n_nu + best_rg - 1) / best_rg;
+    h->asm_cpm = (h->nc + best_rg - 1) / best_rg;
     h->asm_slices = best_slices;
     h->asm_nw = best_nw;
     std::vector<AsmTask> tasks;
@@ -380,10 +380,10 @@ int plan_assembly(rt_handle *h, hipStream_t s) {
     h->d_asm_task = dt;
     int ns_max_m1 = 1;
     for (int n : h->ns) ns_max_m1 = std::max(ns_max_m1, n - 1);
-    const long long per = (long long)ns_max_m1 * h->M * h->n_nu;
+    const long long per = (long long)ns_max_m1 * h->M * h->nc;
     const dim3 grid((unsigned)std::min<long long>((per + 255) / 256, 4096), h->n_atm);
-    hipLaunchKernelGGL(ew_table_kernel, grid, dim3(256), 0, s, h->d_atm, h->d_tau, h->d_opac,
-                       h->d_mu_pos, h->M, h->n_nu, h->fs, h->d_ew);
+    hipLaunchKernelGGL(ew_table_kernel, grid, dim3(256), 0, s, h->d_atm, h->d_tau, h->d_opac_c,
+                       h->d_mu_pos, h->M, h->nc, h->fs, h->d_ew);
     if (hipGetLastError() != hipSuccess) return fail(RT_EDEVICE, "assembly coefficient launch failed");
     return RT_OK;
 }
@@ -404,7 +404,7 @@ int assemble(rt_handle *h, double *A, hipStream_t s) {
     g.sc_stride = h->n_dense;
     g.dg = h->d_asm_dg;
     g.ns_total = h->ns_total;
-    g.n_nu = h->n_nu;
+    g.n_nu = h->nc;
     g.M = h->M;
     g.cpm = h->asm_cpm;
     g.nw = h->asm_nw;

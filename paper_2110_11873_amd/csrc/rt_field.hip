@@ -56,7 +56,9 @@ __global__ __launch_bounds__(kFieldNT) void field_quad_kernel(FieldArgs a) {
     __shared__ double2 part[kFieldNT / kWave];
     const int kk = blockIdx.x;
     const int lane = threadIdx.x % kWave, wv = threadIdx.x / kWave;
-    const AtmDesc at = a.atm[a.pt_atm[kk]];
+    const int slab = a.pt_atm[kk];
+    const AtmDesc at = a.atm[slab];
+    const RayConst *rayc = a.rayc + (long long)slab * a.M * a.n_nu;
     const int k = kk - at.doff, ns = at.ns;
     const long long base = 2LL * a.n_mu * a.n_nu * at.doff;
     const double *FI = a.fin + base + (long long)k * a.n_mu * a.n_nu;
@@ -67,7 +69,7 @@ __global__ __launch_bounds__(kFieldNT) void field_quad_kernel(FieldArgs a) {
         // r runs over (|mu| index, direction, frequency)
         const int mp = r / (2 * a.n_nu), dir = (r / a.n_nu) % 2, p = r % a.n_nu;
         const long long e = (long long)a.mu_idx[2 * mp + dir] * a.n_nu + p;
-        const RayConst rc = a.rayc[at.ray_off + mp * a.n_nu + p];
+        const RayConst rc = rayc[mp * a.n_nu + p];
         const double t2 = t2_of(a.mu_pos[mp]);
         const double I = FI[e], Q = FQ[e];
         J0 = fma(rc.q, I, J0);
@@ -237,7 +239,7 @@ FieldArgs field_args(const rt_handle *h) {
     a.opac = h->d_opac;
     a.mu_pos = h->d_mu_pos;
     a.B = h->d_B;
-    a.rayc = h->d_rayc;
+    a.rayc = h->d_rayc_nu;
     a.dirc = h->d_dirc;
     a.mu_idx = h->d_mu_idx;
     a.fs = h->fs;

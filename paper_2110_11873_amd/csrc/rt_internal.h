@@ -19,7 +19,7 @@ constexpr int kKrylovThreads = 256;
 constexpr int kKrylovEPT = (2 * RT_MAX_NS + kKrylovThreads - 1) / kKrylovThreads;
 
 // Per-slab launch plan of the formal-solver sweep.  A ray is one (|mu_m|, nu_p)
-// pair; its depth recurrence is split into C chunks, one chunk per lane,
+// pair, nu_p standing for all frequencies of equal opacity ratio; its depth recurrence is split into C chunks, one chunk per lane,
 // G = 64 / C rays per wavefront ("wave-batch").  The first nlong chunks have
 // Leff intervals, the others Leff - 1: a short chunk's last step is a
 // zero-length interval (the identity), which is neither stored nor loaded.
@@ -31,7 +31,7 @@ struct AtmDesc {
     int C;          // chunks per ray (power of two, <= 64)
     int Leff;       // intervals of a long chunk (chunk_len; <= the kernel's L)
     int G;          // rays per wave-batch
-    int n_nu;       // frequencies: rays per direction
+    int n_nu;       // distinct opacities: rays per direction (rt_handle::nc)
     int nwb;        // wave-batches per direction
     int ray_off;    // first ray of the slab in the ray tables (rays m*n_nu + p)
     int blk_first;  // first sweep block of the slab
@@ -170,12 +170,12 @@ hipError_t launch_finalize(const SweepArgs &a, int n_atm, int ns_max, int nblk_m
 // may be NULL: not built), the tile-ordered weights and (kappa, 1 / kappa).
 hipError_t launch_coef_build(int nblocks, int W, const AtmDesc *atm, const BlockDesc *blk,
                              const double *tau, const double *opac, const double *mu_pos, int fs,
-                             const double *qray, double2 *coef64, float2 *coef32, double *w64,
+                             const RayConst *rayc, double2 *coef64, float2 *coef32, double *w64,
                              float *w32, double *qtile, double2 *ktile, hipStream_t s);
-hipError_t launch_ray_setup(int n_atm, const AtmDesc *atm, const double *mu_pos,
-                            const double *w_pos, int M, const double *w_nu, const double *phi,
-                            int n_nu, int normalize, RayConst *rayc, double *q, double2 *dirc,
-                            double4 *Qs, hipStream_t s);
+// Ray constants of the n spectral weights w_p phi_p per slab (wphi: n_atm x n).
+hipError_t launch_ray_setup(int n_atm, const double *mu_pos, const double *w_pos, int M,
+                            const double *wphi, int n, int normalize, RayConst *rayc,
+                            double2 *dirc, double4 *Qs, hipStream_t s);
 hipError_t launch_diag(int npts, const int *pt_atm, const AtmDesc *atm, const double *tau,
                        const double *opac, const double *mu_pos, const RayConst *rayc, int M,
                        int n_nu, int fs, double *diag, double *dinv, hipStream_t s);
@@ -253,13 +253,18 @@ struct rt_handle {
     // device copies of the problem
     double *d_tau = nullptr, *d_B = nullptr, *d_opac = nullptr, *d_phi = nullptr;
     double *d_mu_pos = nullptr, *d_w_pos = nullptr, *d_w_nu = nullptr;
+    double *d_wphi = nullptr;     // spectral weights w_p phi_p per slab and frequency
+    // frequencies of equal opacity ratio merged into one ray (complete
+    // redistribution): nc per slab, their opacity ratios and summed weights
+    int nc = 0;
+    double *d_opac_c = nullptr, *d_wphi_c = nullptr;
     int *d_pt_atm = nullptr;
     rt::AtmDesc *d_atm = nullptr;
     rt::BlockDesc *d_blk = nullptr;
     rt::AtmDesc *d_atm_tail = nullptr;  // nblk, blk_first, part_off of the tail plan
     rt::BlockDesc *d_blk_tail = nullptr;
-    rt::RayConst *d_rayc = nullptr;
-    double *d_q = nullptr;        // per ray quadrature weight
+    rt::RayConst *d_rayc = nullptr;     // per merged ray m nc + p of each slab (ray_off)
+    rt::RayConst *d_rayc_nu = nullptr;  // per (|mu|, frequency) m n_nu + p of each slab
     double *d_qt = nullptr;       // tile-ordered, zero-padded quadrature weights
     long long n_qt = 0;
     double2 *d_dirc = nullptr;    // per direction (T1, T1^2 + T2^2)

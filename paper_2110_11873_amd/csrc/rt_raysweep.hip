@@ -252,7 +252,7 @@ __global__ void ray_finalize_kernel(RayArgs a, const int *pt_atm, int npts) {
 }  // namespace
 
 int ray_slots(const rt_handle *h) {
-    return 2 * ((h->M * h->n_nu + kWave - 1) / kWave);
+    return 2 * ((h->M * h->nc + kWave - 1) / kWave);
 }
 
 hipError_t apply_ray_operator(rt_handle *h, const double *in, const double *scale, double *out,
@@ -260,7 +260,7 @@ hipError_t apply_ray_operator(rt_handle *h, const double *in, const double *scal
     RayArgs a{};
     a.atm = h->d_atm;
     a.tau = h->d_tau;
-    a.opac = h->d_opac;
+    a.opac = h->d_opac_c;
     a.mu_pos = h->d_mu_pos;
     a.rayc = h->d_rayc;
     a.sig_in = in;
@@ -271,7 +271,7 @@ hipError_t apply_ray_operator(rt_handle *h, const double *in, const double *scal
     a.B = h->d_B;
     a.fs = h->fs;
     a.M = h->M;
-    a.n_nu = h->n_nu;
+    a.n_nu = h->nc;
     a.slots = ray_slots(h);
     a.mode = mode;
     const int groups = a.slots / 2, per_wg = kRayNT / kWave;

@@ -40,43 +40,41 @@
 namespace rt {
 
 // --------------------------------------------------------------------------
-// Ray constants: q = (w_m / 2) w~_p, w~_p = w_p phi_p (/ sum if normalized),
+// Ray constants of the n spectral weights w_p phi_p of each slab (of every
+// frequency, or of the merged ones): q = (w_m / 2) w_p phi_p (/ sum if normalized),
 // with T1 = sqrt2 (3 mu^2 - 1) / 4, T2 = sqrt2 (3 mu^2 - 3) / 4.
 // One block per slab.
 // --------------------------------------------------------------------------
-__global__ void ray_setup_kernel(const AtmDesc *atm, const double *mu_pos, const double *w_pos,
-                                 int M, const double *w_nu, const double *phi, int n_nu,
-                                 int normalize, RayConst *rayc, double *qray, double2 *dirc,
-                                 double4 *Qs) {
+__global__ void ray_setup_kernel(const double *mu_pos, const double *w_pos, int M,
+                                 const double *wphi, int n, int normalize, RayConst *rayc,
+                                 double2 *dirc, double4 *Qs) {
     __shared__ double red[256 / kWave];
     __shared__ double red3[3 * (256 / kWave)];
     const int a = blockIdx.x;
-    const double *ph = phi + (long long)a * n_nu;
+    const double *wp = wphi + (long long)a * n;
     double norm = 1.0;
     if (normalize) {
         double s = 0.0;
-        for (int p = threadIdx.x; p < n_nu; p += blockDim.x) s += w_nu[p] * ph[p];
+        for (int p = threadIdx.x; p < n; p += blockDim.x) s += wp[p];
         for (int off = kWave / 2; off > 0; off >>= 1) s += __shfl_xor(s, off);
         if ((threadIdx.x & (kWave - 1)) == 0) red[threadIdx.x / kWave] = s;
         __syncthreads();
         norm = 0.0;
         for (int i = 0; i < (int)(blockDim.x / kWave); ++i) norm += red[i];
     }
-    const AtmDesc at = atm[a];
     double sq = 0.0, sq1 = 0.0, sq12 = 0.0;
-    for (int r = threadIdx.x; r < M * n_nu; r += blockDim.x) {
-        const int m = r / n_nu, p = r % n_nu;
+    for (int r = threadIdx.x; r < M * n; r += blockDim.x) {
+        const int m = r / n, p = r % n;
         const double mu2 = mu_pos[m] * mu_pos[m];
         const double t1 = sqrt(2.0) * (3.0 * mu2 - 1.0) / 4.0;
         const double t2 = sqrt(2.0) * (3.0 * mu2 - 3.0) / 4.0;
-        const double q = 0.5 * w_pos[m] * (w_nu[p] * ph[p] / norm);
+        const double q = 0.5 * w_pos[m] * (wp[p] / norm);
         RayConst rc;
         rc.q = q;
         rc.qt1 = q * t1;
         rc.qt12 = q * (t1 * t1 + t2 * t2);
         rc.pad = 0.0;
-        rayc[at.ray_off + r] = rc;
-        qray[at.ray_off + r] = q;
+        rayc[(long long)a * M * n + r] = rc;
         if (a == 0 && p == 0) dirc[m] = make_double2(t1, t1 * t1 + t2 * t2);
         sq += rc.q;
         sq1 += rc.qt1;
@@ -125,7 +123,7 @@ __global__ void ray_setup_kernel(const AtmDesc *atm, const double *mu_pos, const
 // --------------------------------------------------------------------------
 __global__ void coef_build_kernel(int W, const AtmDesc *atm, const BlockDesc *blk,
                                   const double *tau, const double *opac, const double *mu_pos,
-                                  int fs, const double *qray, double2 *coef64, float2 *coef32,
+                                  int fs, const RayConst *rayc, double2 *coef64, float2 *coef32,
                                   double *w64, float *w32, double *qtile, double2 *ktile) {
     const BlockDesc bd = blk[blockIdx.x];
     const AtmDesc at = atm[bd.atm];
@@ -140,7 +138,7 @@ __global__ void coef_build_kernel(int W, const AtmDesc *atm, const BlockDesc *bl
             (p < at.n_nu) ? opac[(long long)bd.atm * at.n_nu + p] / mu_pos[bd.m] : 0.0;
         if (c == 0) {  // per ray: weight, kappa and 1 / kappa (zero for padding rays)
             const long long r = at.q_off + ((long long)bd.m * at.nwb + b) * at.G + g;
-            qtile[r] = (p < at.n_nu) ? qray[at.ray_off + (long long)bd.m * at.n_nu + p] : 0.0;
+            qtile[r] = (p < at.n_nu) ? rayc[at.ray_off + (long long)bd.m * at.n_nu + p].q : 0.0;
             if (ktile) ktile[r] = make_double2(kap, (p < at.n_nu) ? 1.0 / kap : 0.0);
         }
         if (!any) continue;
@@ -402,20 +400,19 @@ int coef_mode_of(const rt_handle *h, bool fp32) { return fp32 ? h->cm32 : h->cm6
 
 hipError_t launch_coef_build(int nblocks, int W, const AtmDesc *atm, const BlockDesc *blk,
                              const double *tau, const double *opac, const double *mu_pos, int fs,
-                             const double *qray, double2 *coef64, float2 *coef32, double *w64,
+                             const RayConst *rayc, double2 *coef64, float2 *coef32, double *w64,
                              float *w32, double *qtile, double2 *ktile, hipStream_t s) {
     if (nblocks <= 0) return hipSuccess;
     hipLaunchKernelGGL(coef_build_kernel, dim3(nblocks), dim3(kWave * W), 0, s, W, atm, blk, tau,
-                       opac, mu_pos, fs, qray, coef64, coef32, w64, w32, qtile, ktile);
+                       opac, mu_pos, fs, rayc, coef64, coef32, w64, w32, qtile, ktile);
     return hipGetLastError();
 }
 
-hipError_t launch_ray_setup(int n_atm, const AtmDesc *atm, const double *mu_pos,
-                            const double *w_pos, int M, const double *w_nu, const double *phi,
-                            int n_nu, int normalize, RayConst *rayc, double *q, double2 *dirc,
-                            double4 *Qs, hipStream_t s) {
-    hipLaunchKernelGGL(ray_setup_kernel, dim3(n_atm), dim3(256), 0, s, atm, mu_pos, w_pos, M,
-                       w_nu, phi, n_nu, normalize, rayc, q, dirc, Qs);
+hipError_t launch_ray_setup(int n_atm, const double *mu_pos, const double *w_pos, int M,
+                            const double *wphi, int n, int normalize, RayConst *rayc,
+                            double2 *dirc, double4 *Qs, hipStream_t s) {
+    hipLaunchKernelGGL(ray_setup_kernel, dim3(n_atm), dim3(256), 0, s, mu_pos, w_pos, M, wphi, n,
+                       normalize, rayc, dirc, Qs);
     return hipGetLastError();
 }
 
