@@ -413,6 +413,7 @@ static SweepArgs sweep_args(rt_handle *h, const double *in, const double *scale,
     a.kt = h->d_kt;
     a.dtau = h->d_dtau;
     a.fs = h->fs;
+    a.M = h->M;
     a.dirc = h->d_dirc;
     a.Qs = h->d_Qs;
     a.sig_in = in;
@@ -657,12 +658,29 @@ int rt_setup(rt_handle **out, const rt_problem *p, const rt_options *o) {
     h->nblk_max = h->nblk_max_tail = 0;
     std::vector<AtmDesc> atm_t(h->n_atm);
     std::vector<BlockDesc> blk_t_h;
-    // Waves per block and wave-batches per wave.  A block never mixes
-    // directions.  Big batches: one block per (slab, direction), the fewest
-    // partial sums; small problems: about 48 blocks in all, for parallelism.
+    // Waves per block, waves per direction and wave-batches per wave.
     h->W = opt.sweep_waves ? opt.sweep_waves : sweep_waves(h->L, false);
     const long long dirs_total = (long long)h->n_atm * h->M;
-    const int blocks_per_dir = (int)std::max<long long>(1, (48 + dirs_total - 1) / dirs_total);
+    long long batches_total = 0;
+    for (int n : h->ns) batches_total += (long long)h->M * slab_tiles(n, h->L, h->nc).nwb;
+    // Big batches: the fewest waves per direction (a power of two) that still
+    // give five waves per SIMD, so that what a wave does once -- sources,
+    // depth steps, the sum over its rays -- is shared by more of its ray
+    // batches.  FP64 / FP32 operator, slabs of 64 to 512 points, 16 directions,
+    // 101 frequencies, us with 4, 2 and 1 waves per direction: 256 slabs
+    // 65 / 35, 61 / 35, 85 / 50; 320 slabs 89 / 41, 85 / 39, 100 / 52; 512
+    // slabs 136 / 66, 126 / 59, 124 / 69; 1024 slabs 263 / 140, 242 / 124,
+    // 233 / 124.
+    int wpd = h->W;
+    if (opt.wave_batches == 0)
+        while (wpd > 1 && dirs_total * (wpd / 2) >= 5 * 4 * 256) wpd /= 2;
+    // Small ones: several blocks per direction, two waves per SIMD in all but
+    // at least two batches per wave (below that a block's fixed part costs
+    // more than the shorter chain saves).  With about 48 blocks in all
+    // instead: one 1024-point slab 30.8 -> 24.6 us FP64, 21.6 -> 16.1 FP32; 8
+    // slabs 16.7 -> 10.4; 32 slabs 22.9 -> 17.7; 64 slabs 24.8 -> 23.0.
+    constexpr long long kFillWaves = 2 * 4 * 256;
+    const int nb_fill = (int)std::max<long long>(2, (batches_total + kFillWaves - 1) / kFillWaves);
     h->atm_h.resize(h->n_atm);
     for (int a = 0; a < h->n_atm; ++a) {
         AtmDesc d{};
@@ -677,12 +695,14 @@ int rt_setup(rt_handle **out, const rt_problem *p, const rt_options *o) {
         d.nwb = t.nwb;
         d.bstride = t.bstride;
         d.ray_off = a * rays;
-        int nb = (d.nwb + h->W * blocks_per_dir - 1) / (h->W * blocks_per_dir);
-        nb = std::min(std::max(nb, 1), 32);
+        int nb = std::min(std::min(nb_fill, 32), (d.nwb + wpd - 1) / wpd);
+        if (wpd < h->W) nb = (d.nwb + wpd - 1) / wpd;
         if (opt.wave_batches > 0) nb = opt.wave_batches;
-        const int wb_per_block = h->W * nb;
+        const int dpb = h->W / wpd;  // directions per block
+        const int dgroups = (h->M + dpb - 1) / dpb;
+        const int wb_per_block = wpd * nb;
         const int blk_per_dir = (d.nwb + wb_per_block - 1) / wb_per_block;
-        d.nblk = h->M * blk_per_dir;
+        d.nblk = dgroups * blk_per_dir;
         d.blk_first = blk;
         d.coef_off = coef;
         d.part_off = part;
@@ -695,14 +715,15 @@ int rt_setup(rt_handle **out, const rt_problem *p, const rt_options *o) {
         d.xi = 1.0 - p->eps[a];
         d.W2 = p->W2[a];
         d.Ibot = p->I_bot ? p->I_bot[a] : (p->B ? p->B[d.doff + d.ns - 1] : 1.0);
-        for (int m = 0; m < h->M; ++m) {
+        for (int mg = 0; mg < dgroups; ++mg) {
             for (int bb = 0; bb < blk_per_dir; ++bb) {
                 BlockDesc bd{};
                 bd.atm = a;
-                bd.m = m;
+                bd.m = mg * dpb;
                 bd.wb_first = bb * wb_per_block;
                 bd.wb_count = std::min(wb_per_block, d.nwb - bd.wb_first);
-                bd.slot = m * blk_per_dir + bb;
+                bd.slot = mg * blk_per_dir + bb;
+                bd.wpd = wpd;
                 h->blk_h.push_back(bd);
             }
         }
@@ -725,6 +746,7 @@ int rt_setup(rt_handle **out, const rt_problem *p, const rt_options *o) {
                     bd.wb_first = bb * wbt;
                     bd.wb_count = std::min(wbt, d.nwb - bd.wb_first);
                     bd.slot = m * bpd + bb;
+                    bd.wpd = h->W;
                     blk_t_h.push_back(bd);
                 }
             }
@@ -880,7 +902,7 @@ int rt_setup(rt_handle **out, const rt_problem *p, const rt_options *o) {
     RT_TRY(hip_check(launch_ray_setup(h->n_atm, h->d_mu_pos, h->d_w_pos, h->M, h->d_wphi_c, h->nc,
                                       h->normalize, h->d_rayc, h->d_dirc, h->d_Qs, s),
                      "ray setup launch"));
-    RT_TRY(hip_check(launch_coef_build(h->n_blocks, h->W, h->d_atm, h->d_blk, h->d_tau,
+    RT_TRY(hip_check(launch_coef_build(h->n_blocks, h->W, h->M, h->d_atm, h->d_blk, h->d_tau,
                                        h->d_opac_c, h->d_mu_pos, h->fs, h->d_rayc, h->d_coef64,
                                        h->d_coef32, h->d_w64, h->d_w32, h->d_qt, h->d_kt, s),
                      "coefficient launch"));

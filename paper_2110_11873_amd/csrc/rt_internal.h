@@ -50,9 +50,9 @@ struct AtmDesc {
     double Ibot;    // bottom inflow for mu > 0
 };
 
-// One sweep block: direction m of slab atm; wave w of a block of W waves
-// handles wave-batches wb_first + w + t * W, t = 0, 1, ..., while below
-// wb_first + wb_count, and writes its quadrature sums to partial-sum slot
+// One sweep block: directions m, m + 1, ... of slab atm, wpd waves each; wave w
+// handles wave-batches wb_first + w % wpd + t * wpd, t = 0, 1, ..., while below
+// wb_first + wb_count, of direction m + w / wpd.  The block writes its quadrature sums to partial-sum slot
 // `slot` of the slab.  The block list is ordered by decreasing work, so the
 // in-order dispatch of workgroups starts the longest ones first.
 struct BlockDesc {
@@ -61,7 +61,8 @@ struct BlockDesc {
     int wb_first;
     int wb_count;
     int slot;
-    int pad[3];
+    int wpd;   // waves per direction: divides the waves of a block
+    int pad[2];
 };
 
 // Quadrature weight of a ray (applied to both directions of the +-mu pair)
@@ -100,6 +101,7 @@ struct SweepArgs {
                              // 0: one shared row filled wave after wave
     int src_lds;             // byte offset of the sources in the sweep's LDS (set at launch)
     int fs;                  // formal solver (coefficients computed in the sweep)
+    int M;                   // directions |mu|
     int part_f32;            // 1: the partial sums are FP32 (written by an FP32 sweep)
 };
 
@@ -168,7 +170,7 @@ hipError_t launch_finalize(const SweepArgs &a, int n_atm, int ns_max, int nblk_m
                            hipStream_t s);
 // Tile-ordered step coefficients of the modes that stream them (any output
 // may be NULL: not built), the tile-ordered weights and (kappa, 1 / kappa).
-hipError_t launch_coef_build(int nblocks, int W, const AtmDesc *atm, const BlockDesc *blk,
+hipError_t launch_coef_build(int nblocks, int W, int M, const AtmDesc *atm, const BlockDesc *blk,
                              const double *tau, const double *opac, const double *mu_pos, int fs,
                              const RayConst *rayc, double2 *coef64, float2 *coef32, double *w64,
                              float *w32, double *qtile, double2 *ktile, hipStream_t s);

@@ -121,7 +121,7 @@ __global__ void ray_setup_kernel(const double *mu_pos, const double *w_pos, int 
 // (kappa, 1 / kappa) are laid out by slot (q_off + (m*nwb + b)*G + slot),
 // zero for padding rays, so the sweep never masks a loaded value.
 // --------------------------------------------------------------------------
-__global__ void coef_build_kernel(int W, const AtmDesc *atm, const BlockDesc *blk,
+__global__ void coef_build_kernel(int M, const AtmDesc *atm, const BlockDesc *blk,
                                   const double *tau, const double *opac, const double *mu_pos,
                                   int fs, const RayConst *rayc, double2 *coef64, float2 *coef32,
                                   double *w64, float *w32, double *qtile, double2 *ktile) {
@@ -132,13 +132,15 @@ __global__ void coef_build_kernel(int W, const AtmDesc *atm, const BlockDesc *bl
     const int s0 = c * (at.Leff - 1) + min(c, at.nlong);
     const bool longc = c < at.nlong;
     const bool any = coef64 || coef32 || w64 || w32;
-    for (int b = bd.wb_first + wave; b < bd.wb_first + bd.wb_count; b += W) {
+    const int m = bd.m + wave / bd.wpd;
+    if (m >= M) return;
+    for (int b = bd.wb_first + wave % bd.wpd; b < bd.wb_first + bd.wb_count; b += bd.wpd) {
         const int p = b * at.G + g;
         const double kap =
-            (p < at.n_nu) ? opac[(long long)bd.atm * at.n_nu + p] / mu_pos[bd.m] : 0.0;
+            (p < at.n_nu) ? opac[(long long)bd.atm * at.n_nu + p] / mu_pos[m] : 0.0;
         if (c == 0) {  // per ray: weight, kappa and 1 / kappa (zero for padding rays)
-            const long long r = at.q_off + ((long long)bd.m * at.nwb + b) * at.G + g;
-            qtile[r] = (p < at.n_nu) ? rayc[at.ray_off + (long long)bd.m * at.n_nu + p].q : 0.0;
+            const long long r = at.q_off + ((long long)m * at.nwb + b) * at.G + g;
+            qtile[r] = (p < at.n_nu) ? rayc[at.ray_off + (long long)m * at.n_nu + p].q : 0.0;
             if (ktile) ktile[r] = make_double2(kap, (p < at.n_nu) ? 1.0 / kap : 0.0);
         }
         if (!any) continue;
@@ -151,7 +153,7 @@ __global__ void coef_build_kernel(int W, const AtmDesc *atm, const BlockDesc *bl
                 const double d = kap * (tau[at.doff + j + 1] - tau[at.doff + j]);
                 step_ew(fs, d, E, w);
             }
-            const long long e = at.coef_off + ((long long)bd.m * at.nwb + b) * at.bstride +
+            const long long e = at.coef_off + ((long long)m * at.nwb + b) * at.bstride +
                                 (last ? (long long)(at.Leff - 1) * kWave + g * at.nlong + c
                                       : (long long)i * kWave + lane);
             if (coef64) coef64[e] = make_double2(E, w);
@@ -398,12 +400,12 @@ hipError_t launch_sweep(int L, int W, bool pf, bool fp32, int cm, const SweepArg
 
 int coef_mode_of(const rt_handle *h, bool fp32) { return fp32 ? h->cm32 : h->cm64; }
 
-hipError_t launch_coef_build(int nblocks, int W, const AtmDesc *atm, const BlockDesc *blk,
+hipError_t launch_coef_build(int nblocks, int W, int M, const AtmDesc *atm, const BlockDesc *blk,
                              const double *tau, const double *opac, const double *mu_pos, int fs,
                              const RayConst *rayc, double2 *coef64, float2 *coef32, double *w64,
                              float *w32, double *qtile, double2 *ktile, hipStream_t s) {
     if (nblocks <= 0) return hipSuccess;
-    hipLaunchKernelGGL(coef_build_kernel, dim3(nblocks), dim3(kWave * W), 0, s, W, atm, blk, tau,
+    hipLaunchKernelGGL(coef_build_kernel, dim3(nblocks), dim3(kWave * W), 0, s, M, atm, blk, tau,
                        opac, mu_pos, fs, rayc, coef64, coef32, w64, w32, qtile, ktile);
     return hipGetLastError();
 }

@@ -145,14 +145,13 @@ __device__ inline double dpp(double v, double old) {
                                                0xF, false);
     return __hiloint2double(hi, lo);
 }
-// As dpp, for values whose lanes without a source are never used (no old
-// value to set up).
+// As dpp, with zero in the lanes without a source (no old value to set up).
 template <int CTRL>
-__device__ inline float dpp_any(float v) {
+__device__ inline float dpp_zero(float v) {
     return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xF, 0xF, true));
 }
 template <int CTRL>
-__device__ inline double dpp_any(double v) {
+__device__ inline double dpp_zero(double v) {
     const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xF, 0xF, true);
     const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xF, 0xF, true);
     return __hiloint2double(hi, lo);
@@ -165,31 +164,37 @@ __device__ inline double read_lane(double v, int l) {
                             __builtin_amdgcn_readlane(__double2loint(v), l));
 }
 
-// A chunk's map x -> P x + (U, V) preceded by the map (pP, pU, pV) of the
-// chunks the radiation crosses before it.
-template <typename T>
-__device__ inline void compose(T &P, T &U, T &V, T pP, T pU, T pV) {
-    U = fma(P, pU, U);
-    V = fma(P, pV, V);
-    P = P * pP;
+// One level of the scan: a chunk's map x -> P x + (U, V) preceded by the map
+// (pP, pU, pV) of the chunks the radiation crosses before it, held by the lane
+// CTRL points to.  Lanes without a source lane keep U and V by adding zeros,
+// which the moves give without an old value to set up.  They keep P where a
+// later level may need it: not where the ray's chunks all sit in one row of
+// lanes (KEEP = false), whose lanes without a source have their final U and V,
+// since the boundary chunk's map contains what enters there.  In FP64 this and
+// entry_down / entry_up took a batch of 8 steps from 363 to 270 VALU operations.
+template <int CTRL, int ROWS, bool KEEP>
+__device__ inline void scan_level_from(double &P, double &U, double &V, double sP, double sU,
+                                       double sV) {
+    if constexpr (ROWS == 0xF) {
+        U = fma(P, dpp_zero<CTRL>(sU), U);
+        V = fma(P, dpp_zero<CTRL>(sV), V);
+    } else {
+        U = fma(P, dpp<CTRL, ROWS>(sU, 0.0), U);
+        V = fma(P, dpp<CTRL, ROWS>(sV, 0.0), V);
+    }
+    if constexpr (KEEP)
+        P *= dpp<CTRL, ROWS>(sP, 1.0);
+    else
+        P *= dpp_zero<CTRL>(sP);
 }
-template <int CTRL, int ROWS, typename T>
-__device__ inline void scan_level(T &P, T &U, T &V) {
-    compose(P, U, V, dpp<CTRL, ROWS>(P, (T)1), dpp<CTRL, ROWS>(U, (T)0),
-            dpp<CTRL, ROWS>(V, (T)0));
-}
-
-// Compose with the map held by (sP, sU, sV) in the lane CTRL points to.
-template <int CTRL, int ROWS, typename T>
-__device__ inline void scan_level_from(T &P, T &U, T &V, T sP, T sU, T sV) {
-    compose(P, U, V, dpp<CTRL, ROWS>(sP, (T)1), dpp<CTRL, ROWS>(sU, (T)0),
-            dpp<CTRL, ROWS>(sV, (T)0));
+template <int CTRL, int ROWS, bool KEEP>
+__device__ inline void scan_level(double &P, double &U, double &V) {
+    scan_level_from<CTRL, ROWS, KEEP>(P, U, V, P, U, V);
 }
 
 // The same level in FP32 as three DPP-sourced VALU operations: the neighbour's
 // U, V and P are read through the DPP operand, and lanes with no source lane
-// (or in rows not enabled) are not written, i.e. keep their own map, which is
-// the composition with the identity.  The leading s_nop covers the wait
+// (or in rows not enabled) are not written, i.e. keep their own map.  The leading s_nop covers the wait
 // states a DPP read needs after a VALU write of its source (2) or of EXEC
 // (5); the trailing one covers a DPP read of the outputs right after.
 #define RT_DPP_SCAN_F32(P, U, V, CTL)                                     \
@@ -200,7 +205,7 @@ __device__ inline void scan_level_from(T &P, T &U, T &V, T sP, T sU, T sV) {
         "s_nop 1"                                                         \
         : "+v"(P), "+v"(U), "+v"(V))
 
-template <int CTRL, int ROWS>
+template <int CTRL, int ROWS, bool KEEP>
 __device__ inline void scan_level(float &P, float &U, float &V) {
     if constexpr (CTRL == kRowShr + 1) RT_DPP_SCAN_F32(P, U, V, "row_shr:1 row_mask:0xf bank_mask:0xf");
     else if constexpr (CTRL == kRowShr + 2) RT_DPP_SCAN_F32(P, U, V, "row_shr:2 row_mask:0xf bank_mask:0xf");
@@ -214,9 +219,10 @@ __device__ inline void scan_level(float &P, float &U, float &V) {
     else if constexpr (CTRL == kRowBcast31 && ROWS == 0xC) RT_DPP_SCAN_F32(P, U, V, "row_bcast:31 row_mask:0xc bank_mask:0xf");
     else static_assert(CTRL < 0, "no FP32 scan level for this DPP control");
 }
-template <>
-__device__ inline void scan_level_from<kRowNewBcast15, 0x5, float>(float &P, float &U, float &V,
-                                                                  float sP, float sU, float sV) {
+template <int CTRL, int ROWS, bool KEEP>
+__device__ inline void scan_level_from(float &P, float &U, float &V, float sP, float sU,
+                                       float sV) {
+    static_assert(CTRL == kRowNewBcast15 && ROWS == 0x5, "no FP32 scan level for this DPP control");
     asm("s_nop 4\n\t"
         "v_fmac_f32_dpp %1, %4, %0 row_newbcast:15 row_mask:0x5 bank_mask:0xf\n\t"
         "v_fmac_f32_dpp %2, %5, %0 row_newbcast:15 row_mask:0x5 bank_mask:0xf\n\t"
@@ -233,36 +239,54 @@ __device__ inline void scan_level_from<kRowNewBcast15, 0x5, float>(float &P, flo
 // Row shifts by 1, 2, 4, 8 lanes are chunk shifts by 1, 2, 4, 8 / s.
 template <int C, typename T>
 __device__ inline void scan_forward(T &P, T &U, T &V) {
-    if constexpr (C >= 16) scan_level<kRowShr + 1, 0xF>(P, U, V);
-    if constexpr (C >= 8) scan_level<kRowShr + 2, 0xF>(P, U, V);
-    if constexpr (C >= 4) scan_level<kRowShr + 4, 0xF>(P, U, V);
-    if constexpr (C >= 2) scan_level<kRowShr + 8, 0xF>(P, U, V);
-    if constexpr (C >= 32) scan_level<kRowBcast15, 0xA>(P, U, V);  // rows 1, 3 <- lane 15 of 0, 2
-    if constexpr (C == 64) scan_level<kRowBcast31, 0xC>(P, U, V);  // rows 2, 3 <- lane 31
+    if constexpr (C >= 16) scan_level<kRowShr + 1, 0xF, (C > 16)>(P, U, V);
+    if constexpr (C >= 8) scan_level<kRowShr + 2, 0xF, (C > 16)>(P, U, V);
+    if constexpr (C >= 4) scan_level<kRowShr + 4, 0xF, (C > 16)>(P, U, V);
+    if constexpr (C >= 2) scan_level<kRowShr + 8, 0xF, (C > 16)>(P, U, V);
+    if constexpr (C >= 32) scan_level<kRowBcast15, 0xA, true>(P, U, V);  // rows 1, 3 <- lane 15 of 0, 2
+    if constexpr (C == 64) scan_level<kRowBcast31, 0xC, true>(P, U, V);  // rows 2, 3 <- lane 31
 }
 template <int C, typename T>
 __device__ inline void scan_backward(T &P, T &U, T &V, int lane) {
-    if constexpr (C >= 16) scan_level<kRowShl + 1, 0xF>(P, U, V);
-    if constexpr (C >= 8) scan_level<kRowShl + 2, 0xF>(P, U, V);
-    if constexpr (C >= 4) scan_level<kRowShl + 4, 0xF>(P, U, V);
-    if constexpr (C >= 2) scan_level<kRowShl + 8, 0xF>(P, U, V);
+    if constexpr (C >= 16) scan_level<kRowShl + 1, 0xF, (C > 16)>(P, U, V);
+    if constexpr (C >= 8) scan_level<kRowShl + 2, 0xF, (C > 16)>(P, U, V);
+    if constexpr (C >= 4) scan_level<kRowShl + 4, 0xF, (C > 16)>(P, U, V);
+    if constexpr (C >= 2) scan_level<kRowShl + 8, 0xF, (C > 16)>(P, U, V);
     if constexpr (C >= 32) {
         // rows 0 and 2 take the first lane of rows 1 and 3: the wave shifted
         // left by one lane puts lanes 16 and 48 at lanes 15 and 47, which are
         // then broadcast over rows 0 and 2 (only those two lanes of the shift
         // are read, and both have a source)
-        scan_level_from<kRowNewBcast15, 0x5>(P, U, V, dpp_any<kWaveShl1>(P), dpp_any<kWaveShl1>(U),
-                                             dpp_any<kWaveShl1>(V));
+        scan_level_from<kRowNewBcast15, 0x5, true>(P, U, V, dpp_zero<kWaveShl1>(P), dpp_zero<kWaveShl1>(U),
+                                             dpp_zero<kWaveShl1>(V));
     }
-    if constexpr (C == 64) {  // lanes 0..31 take lane 32
-        const T rP = read_lane(P, 32), rU = read_lane(U, 32), rV = read_lane(V, 32);
-        const bool lo = lane < 32;
-        compose(P, U, V, lo ? rP : (T)1, lo ? rU : (T)0, lo ? rV : (T)0);
+    if constexpr (C == 64) {  // lanes 0..31 take lane 32; P is not used again
+        const T rU = read_lane(U, 32), rV = read_lane(V, 32);
+        const T Plo = lane < 32 ? P : (T)0;
+        U = fma(Plo, rU, U);
+        V = fma(Plo, rV, V);
     }
 }
 
-// The value held by chunk c - 1 (from_prev) or c + 1 (from_next) of the same
-// ray; `old` where there is no such chunk.
+// The value at the end of the neighbouring chunk (c - 1 for downward, c + 1 for
+// upward rays) of the same ray, or `enter` at the chunk where the ray enters
+// (inner = 0 there and 1 elsewhere; enter = 0 elsewhere).
+template <int C, typename T>
+__device__ inline T entry_down(T v, T enter, T inner) {
+    if constexpr (C >= 32)
+        return fma(dpp_zero<kWaveShr1>(v), inner, enter);
+    else
+        return dpp_zero<kRowShr + 16 / C>(v) + enter;
+}
+template <int C, typename T>
+__device__ inline T entry_up(T v, T enter, T inner) {
+    if constexpr (C >= 32)
+        return fma(dpp_zero<kWaveShl1>(v), inner, enter);
+    else
+        return dpp_zero<kRowShl + 16 / C>(v) + enter;
+}
+
+// The value held by chunk c - 1 of the same ray; `old` where there is none.
 template <int C, typename T>
 __device__ inline T from_prev(T v, T old, int c) {
     if constexpr (C >= 32) {
@@ -272,18 +296,9 @@ __device__ inline T from_prev(T v, T old, int c) {
         return dpp<kRowShr + 16 / C, 0xF>(v, old);
     }
 }
-template <int C, typename T>
-__device__ inline T from_next(T v, T old, int c) {
-    if constexpr (C >= 32) {
-        const T x = dpp<kWaveShl1, 0xF>(v, old);
-        return c == C - 1 ? old : x;
-    } else {
-        return dpp<kRowShl + 16 / C, 0xF>(v, old);
-    }
-}
-
-// One wave's share of a block: the ray batches wb_first + wave + t * W of
-// direction bd.m of slab bd.atm, whose chunk count is C and chunk length LE.
+// One wave's share of a block: the ray batches wb_first + wave % wpd + t * wpd
+// of direction m = bd.m + wave / wpd (none past the last direction) of slab
+// bd.atm, whose chunk count is C and chunk length LE.
 template <typename T, int LE, int C, int W, int PF, int CM>
 __device__ __forceinline__ void sweep_rays(const SweepArgs &a, const BlockDesc &bd,
                                            const AtmDesc &at, int wave, int lane, T *sacc,
@@ -345,7 +360,7 @@ __device__ __forceinline__ void sweep_rays(const SweepArgs &a, const BlockDesc &
     }
 
     // AU = sum_rays q (D from s00), AV = sum_rays q (D from s20), by point;
-    // every ray of the block has the same direction, so the T factors are
+    // every ray of the wave has the same direction, so the T factors are
     // applied once at the end
     T AU[LE + 1], AV[LE + 1];
 #pragma unroll
@@ -363,6 +378,11 @@ __device__ __forceinline__ void sweep_rays(const SweepArgs &a, const BlockDesc &
     // that ends the last chunk has the bottom inflow's upward deviation
     const T ftop = (c == 0) ? (T)1 : (T)0;
     const T fbot = (c == C - 1 && bottom_on_grid) ? (T)1 : (T)0;
+    // what enters the ray, at the chunk where it enters, and which chunks are
+    // entered from a neighbour
+    const T in_d0 = (c == 0) ? topD0 : (T)0, in_d2 = (c == 0) ? topD2 : (T)0;
+    const T in_u0 = (c == C - 1) ? botD0 : (T)0, in_u2 = (c == C - 1) ? botD2 : (T)0;
+    const T inner_d = (c == 0) ? (T)0 : (T)1, inner_u = (c == C - 1) ? (T)0 : (T)1;
 
     // this direction's tiles and ray weights, read through buffer
     // descriptors that end at the block's last batch: a load of a batch past
@@ -370,13 +390,14 @@ __device__ __forceinline__ void sweep_rays(const SweepArgs &a, const BlockDesc &
     // nothing, so every load is unconditional and the compiler can keep the
     // next batch's loads in flight across the current batch's work.  Batch
     // and lane offsets in a register, the step offset in a scalar register.
-    const int bend = bd.wb_first + bd.wb_count;
+    const int wpd = bd.wpd, m = min(bd.m + wave / wpd, a.M - 1);
+    const int bend = bd.m + wave / wpd < a.M ? bd.wb_first + bd.wb_count : 0;
     const int bbytes = at.bstride * (int)sizeof(Ent);  // one wave-batch of tile entries
     const Ent *tiles = reinterpret_cast<const Ent *>(a.coef) + at.coef_off +
-                       (long long)bd.m * at.nwb * at.bstride;
+                       (long long)m * at.nwb * at.bstride;
     const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
         (void *)tiles, 0, CM == kCoefRecompute ? 0 : bend * bbytes, kRawBufferWord3);
-    const long long rdir = at.q_off + (long long)bd.m * at.nwb * at.G;
+    const long long rdir = at.q_off + (long long)m * at.nwb * at.G;
     const __amdgpu_buffer_rsrc_t qrsrc =
         __builtin_amdgcn_make_buffer_rsrc((void *)(a.q + rdir), 0, bend * at.G * 8, kRawBufferWord3);
     // per ray (kappa, 1 / kappa), laid out as the weights; zero for padding rays
@@ -438,89 +459,81 @@ __device__ __forceinline__ void sweep_rays(const SweepArgs &a, const BlockDesc &
                 for (int i = 0; i < LE; ++i) Es[i] = ws[i] = recip(fma(kap, dt[i], (T)1));
             }
         }
-        // one pass over the chunk with zero inflow in both directions: the
-        // local deviations go into the quadrature at once.  p = w (S_u - S_k)
-        // is formed once per step and source and serves both directions; the
-        // running transmissions Td[i] = E_0..E_i, Tu[i] = E_i..E_{LE-1} are
-        // kept for the inflow term added after the scan
-        T p0[LE], p2[LE], Td[LE], Tu[LE];
+        // First pass over the chunk with zero inflow in both directions: its
+        // map D_out = P D_in + (U, V) per direction.  p = w (S_u - S_k) is
+        // formed once per step and source and serves both directions and
+        // passes; one product of E serves both directions.
+        T p0[LE], p2[LE];
 #pragma unroll
         for (int i = 0; i < LE; ++i) {
             p0[i] = ws[i] * dl0[i];
             p2[i] = ws[i] * dl2[i];
         }
-        T dU = p0[0], dV = p2[0];
-        Td[0] = Es[0];
-        AU[1] = fma(q, dU, AU[1]);
-        AV[1] = fma(q, dV, AV[1]);
+        T dU = p0[0], dV = p2[0], uU = -p0[LE - 1], uV = -p2[LE - 1], Pd = Es[0];
 #pragma unroll
         for (int i = 1; i < LE; ++i) {
             dU = fma(Es[i], dU, p0[i]);
             dV = fma(Es[i], dV, p2[i]);
-            Td[i] = Td[i - 1] * Es[i];
-            AU[i + 1] = fma(q, dU, AU[i + 1]);
-            AV[i + 1] = fma(q, dV, AV[i + 1]);
+            uU = fma(Es[LE - 1 - i], uU, -p0[LE - 1 - i]);
+            uV = fma(Es[LE - 1 - i], uV, -p2[LE - 1 - i]);
+            Pd *= Es[i];
         }
-        T uU = -p0[LE - 1], uV = -p2[LE - 1];
-        Tu[LE - 1] = Es[LE - 1];
-        AU[LE - 1] = fma(q, uU, AU[LE - 1]);
-        AV[LE - 1] = fma(q, uV, AV[LE - 1]);
-#pragma unroll
-        for (int i = LE - 2; i >= 0; --i) {
-            uU = fma(Es[i], uU, -p0[i]);
-            uV = fma(Es[i], uV, -p2[i]);
-            Tu[i] = Tu[i + 1] * Es[i];
-            AU[i] = fma(q, uU, AU[i]);
-            AV[i] = fma(q, uV, AV[i]);
-        }
+        T Pu = Pd;
+        // the boundary chunks' maps with what enters there
+        dU = fma(Pd, in_d0, dU);
+        dV = fma(Pd, in_d2, dV);
+        uU = fma(Pu, in_u0, uU);
+        uV = fma(Pu, in_u2, uV);
 
-        // lane scans of the chunk maps D_out = P D_in + e: downward chunks
-        // compose in chunk order, upward ones in reverse order
-        T Pd = Td[LE - 1], Pu = Tu[0];
+        // lane scans of the chunk maps: downward chunks compose in chunk
+        // order, upward ones in reverse order
         scan_forward<C>(Pd, dU, dV);
         scan_backward<C>(Pu, uU, uV, lane);
-        // deviations at the chunk's entry points: the boundary deviation
-        // carried through the chunks above (down) or below (up) -- the value
-        // at the end of the neighbouring chunk -- or the boundary's own
-        const T qdU = q * from_prev<C, T>(fma(Pd, topD0, dU), topD0, c);
-        const T qdV = q * from_prev<C, T>(fma(Pd, topD2, dV), topD2, c);
-        const T quU = q * from_next<C, T>(fma(Pu, botD0, uU), botD0, c);
-        const T quV = q * from_next<C, T>(fma(Pu, botD2, uV), botD2, c);
+        // deviations at the chunk's entry points
+        T xdU = entry_down<C>(dU, in_d0, inner_d), xdV = entry_down<C>(dV, in_d2, inner_d);
+        T xuU = entry_up<C>(uU, in_u0, inner_u), xuV = entry_up<C>(uV, in_u2, inner_u);
+        AU[0] = fma(ftop * q, xdU, AU[0]);
+        AV[0] = fma(ftop * q, xdV, AV[0]);
+        AU[LE] = fma(fbot * q, xuU, AU[LE]);
+        AV[LE] = fma(fbot * q, xuV, AV[LE]);
 
-        // inflow terms: D_true = D_local + T * D_in at every point of the chunk
+        // Second pass from the true inflow, into the quadrature.  Keeping
+        // the transmissions of the first pass and adding T D_in instead took
+        // one operation more per step and 2 LE registers.
 #pragma unroll
         for (int i = 0; i < LE; ++i) {
-            AU[i + 1] = fma(Td[i], qdU, AU[i + 1]);
-            AV[i + 1] = fma(Td[i], qdV, AV[i + 1]);
-            AU[i] = fma(Tu[i], quU, AU[i]);
-            AV[i] = fma(Tu[i], quV, AV[i]);
+            xdU = fma(Es[i], xdU, p0[i]);
+            xdV = fma(Es[i], xdV, p2[i]);
+            AU[i + 1] = fma(q, xdU, AU[i + 1]);
+            AV[i + 1] = fma(q, xdV, AV[i + 1]);
+            const int j = LE - 1 - i;
+            xuU = fma(Es[j], xuU, -p0[j]);
+            xuV = fma(Es[j], xuV, -p2[j]);
+            AU[j] = fma(q, xuU, AU[j]);
+            AV[j] = fma(q, xuV, AV[j]);
         }
-        AU[0] = fma(ftop, qdU, AU[0]);
-        AV[0] = fma(ftop, qdV, AV[0]);
-        AU[LE] = fma(fbot, quU, AU[LE]);
-        AV[LE] = fma(fbot, quV, AV[LE]);
     };
 
-    const int b0 = bd.wb_first + wave;
+    const int b0 = bd.wb_first + wave % wpd;
     if constexpr (PF == 0) {
-        for (int b = b0; b < bend; b += W) {
+        for (int b = b0; b < bend; b += wpd) {
             Ent cn[LE];
             double qn;
             double2 kn = make_double2(0.0, 0.0);
             load_batch(b, cn, qn, kn);
             process(cn, qn, kn);
         }
-    } else {
+    } else if (b0 < bend) {
         // two register sets, each loaded one batch ahead of its use
         Ent cA[LE], cB[LE];
         double qA, qB;
         double2 kA = make_double2(0.0, 0.0), kB = kA;
         load_batch(b0, cA, qA, kA);
-        for (int b = b0; b < bend; b += 2 * W) {
-            load_batch(b + W, cB, qB, kB);
+        for (int b = b0; b < bend; b += 2 * wpd) {
+            load_batch(b + wpd, cB, qB, kB);
             process(cA, qA, kA);
-            if (b + W >= bend) break;
-            load_batch(b + 2 * W, cA, qA, kA);
+            if (b + wpd >= bend) break;
+            load_batch(b + 2 * wpd, cA, qA, kA);
             process(cB, qB, kB);
         }
     }
@@ -545,7 +558,7 @@ __device__ __forceinline__ void sweep_rays(const SweepArgs &a, const BlockDesc &
     const T bU = AU[LE], bV = AV[LE];
 
     // J00 = AU + T1 AV, J20 = T1 AU + (T1^2 + T2^2) AV for this direction
-    const double2 tf = a.dirc[bd.m];
+    const double2 tf = a.dirc[m];
     const T t1 = (T)tf.x, t12 = (T)tf.y;
 
     // block totals of the 2 ns quadrature sums, stored in the sweep's type
@@ -632,7 +645,7 @@ __device__ __forceinline__ void dispatch_le(const SweepArgs &a, const BlockDesc 
 template <typename T, int L, int CM>
 struct MinWaves {
     static constexpr int value =
-        (L == 8 && CM == kCoefW) ? (sizeof(T) == 4 ? 5 : 3) : 1;
+        (L == 8 && CM == kCoefW) ? (sizeof(T) == 4 ? 4 : 3) : 1;
 };
 
 // LDS: the quadrature rows (a.rows ? W : 1) x 2 ns_max values of type T, then
