@@ -58,8 +58,9 @@ extern "C" {
 /* DELO-parabolic (Sect. 4.1): the source interpolated by the parabola through
  * the upwind, current and downwind points of the ray, integrated exactly; the
  * last point of a ray takes the DELO-linear step.  Without dichroism, as
- * here, DELOPAR is the same step.  Its operator runs a ray-per-lane FP64
- * sweep (also in RT_PREC_MIXED); rt_assemble, rt_solve_lu and the SOR/SSOR
+ * here, DELOPAR is the same step.  Its operator sweeps in FP64 (also in
+ * RT_PREC_MIXED), with streamed coefficients of its own (rt_options.coef_mode
+ * does not matter); rt_assemble, rt_solve_lu and the SOR/SSOR
  * preconditioners are not available for it (RT_EINVAL). */
 #define RT_FS_DELO_PARABOLIC 3
 

@@ -21,8 +21,8 @@ INCLUDE = os.path.join(ROOT, "include")
 OUT = os.path.join(PKG, "librt.so")
 SOURCES = ["rt_api.hip", "rt_sweep.hip", "rt_sweep_f32.hip", "rt_sweep_f64.hip",
            "rt_sweep_f32_w.hip", "rt_sweep_f64_w.hip", "rt_sweep_f32_rc.hip", "rt_sweep_f64_rc.hip",
-           "rt_krylov.hip",
-           "rt_assemble.hip", "rt_dense.hip", "rt_raysweep.hip", "rt_field.hip",
+           "rt_sweep_f64_par.hip", "rt_krylov.hip",
+           "rt_assemble.hip", "rt_dense.hip", "rt_field.hip",
            "rt_fieldsolve.hip", "rt_prd.hip", "rt_noalloc.hip"]
 OBJDIR = os.path.join(PKG, "_build")
 # the sources of the sweep's kernels and launchers: their hash is built into
@@ -30,7 +30,7 @@ OBJDIR = os.path.join(PKG, "_build")
 # while it is unchanged
 SWEEP_SOURCES = ["rt_sweep_kernel.h", "rt_sweep.hip", "rt_sweep_f32.hip", "rt_sweep_f64.hip",
                  "rt_sweep_f32_w.hip", "rt_sweep_f64_w.hip", "rt_sweep_f32_rc.hip",
-                 "rt_sweep_f64_rc.hip", "rt_coef.h"]
+                 "rt_sweep_f64_rc.hip", "rt_sweep_f64_par.hip", "rt_coef.h"]
 
 
 def sweep_source_hash() -> str:

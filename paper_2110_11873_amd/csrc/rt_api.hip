@@ -407,7 +407,8 @@ static SweepArgs sweep_args(rt_handle *h, const double *in, const double *scale,
     a.atm = plan_atm(h);
     a.blk = plan_blk(h);
     const int cm = coef_mode_of(h, fp32);
-    a.coef = cm == kCoefPairs ? (fp32 ? (const void *)h->d_coef32 : (const void *)h->d_coef64)
+    a.coef = cm == kCoefParabolic ? (const void *)h->d_coef64
+             : cm == kCoefPairs ? (fp32 ? (const void *)h->d_coef32 : (const void *)h->d_coef64)
                               : (fp32 ? (const void *)h->d_w32 : (const void *)h->d_w64);
     a.q = h->d_qt;
     a.kt = h->d_kt;
@@ -429,6 +430,7 @@ static SweepArgs sweep_args(rt_handle *h, const double *in, const double *scale,
 
 hipError_t apply_sweep(rt_handle *h, const double *in, const double *scale, const int *mask,
                        bool fp32, hipStream_t s) {
+    fp32 = sweeps_fp32(h, fp32);
     const SweepArgs a = sweep_args(h, in, scale, nullptr, mask, fp32, 0);
     int W;
     bool pf;
@@ -452,7 +454,7 @@ hipError_t apply_operator_into(rt_handle *h, const double *in, double *out, doub
 
 hipError_t apply_operator(rt_handle *h, const double *in, const double *scale, double *out,
                           const int *mask, bool fp32, int mode, hipStream_t s) {
-    if (h->fs == RT_FS_DELO_PARABOLIC) return apply_ray_operator(h, in, scale, out, mask, mode, s);
+    fp32 = sweeps_fp32(h, fp32);
     const SweepArgs a = sweep_args(h, in, scale, out, mask, fp32, mode);
     int W;
     bool pf;
@@ -560,7 +562,7 @@ void rt_destroy(rt_handle *h) {
                     h->d_cq,    h->d_state, h->d_active,  h->d_cycle,   h->d_count,
                     h->d_ew,    h->d_asm_dg, h->d_asm_sc, h->d_asm_task, h->d_A,
                     h->d_pz,    h->d_ones,  h->d_LU,      h->d_piv,     h->d_sing,
-                    h->d_rpart, h->d_mu_idx, h->d_fsig, h->d_Rw,   h->d_Rw_bf, h->d_prd_Jm,
+                    h->d_mu_idx, h->d_fsig, h->d_Rw,   h->d_Rw_bf, h->d_prd_Jm,
                     h->d_prd_J, h->d_prd_diag, h->d_prd_dinv, h->d_w64, h->d_w32, h->d_kt,
                     h->d_dtau, h->seg_ws[0], h->seg_ws[1], h->d_lu_order};
     clear_graphs(h);
@@ -800,9 +802,8 @@ int rt_setup(rt_handle **out, const rt_problem *p, const rt_options *o) {
         }
     };
     order_blocks(h->blk_h);
-    // the tail plan only where it differs (not for the three-point solver,
-    // whose operator does not use the sweep blocks)
-    const bool tail_plan = blk_t != blk && h->fs != RT_FS_DELO_PARABOLIC;
+    // the tail plan only where it differs
+    const bool tail_plan = blk_t != blk;
     if (tail_plan) {
         order_blocks(blk_t_h);
         h->n_blocks_tail = blk_t;
@@ -853,11 +854,12 @@ int rt_setup(rt_handle **out, const rt_problem *p, const rt_options *o) {
     RT_TRY(dalloc(&h->d_Qs, (size_t)h->n_atm));
     // the coefficient tiles the handle's sweeps stream, (kappa, 1 / kappa) per
     // ray and the depth steps for those that derive coefficients
-    if (h->cm64 == kCoefPairs) RT_TRY(dalloc(&h->d_coef64, h->n_pairs));
-    if (h->cm32 == kCoefPairs) RT_TRY(dalloc(&h->d_coef32, h->n_pairs));
-    if (h->cm64 == kCoefW) RT_TRY(dalloc(&h->d_w64, h->n_pairs));
-    if (h->cm32 == kCoefW) RT_TRY(dalloc(&h->d_w32, h->n_pairs));
-    const bool derive = h->cm64 != kCoefPairs || h->cm32 != kCoefPairs;
+    const int cm64 = coef_mode_of(h, false), cm32 = coef_mode_of(h, true);
+    if (cm64 == kCoefPairs || cm64 == kCoefParabolic) RT_TRY(dalloc(&h->d_coef64, h->n_pairs));
+    if (cm32 == kCoefPairs) RT_TRY(dalloc(&h->d_coef32, h->n_pairs));
+    if (cm64 == kCoefW) RT_TRY(dalloc(&h->d_w64, h->n_pairs));
+    if (cm32 == kCoefW) RT_TRY(dalloc(&h->d_w32, h->n_pairs));
+    const bool derive = cm64 != kCoefPairs || cm32 != kCoefPairs;
     if (derive) {
         RT_TRY(dalloc(&h->d_kt, (size_t)h->n_qt));
         RT_TRY(dalloc(&h->d_dtau, acc));
@@ -871,8 +873,6 @@ int rt_setup(rt_handle **out, const rt_problem *p, const rt_options *o) {
     RT_TRY(dalloc(&h->d_diag, h->n_unk));
     RT_TRY(dalloc(&h->d_dinv, h->n_unk));
     RT_TRY(dalloc(&h->d_b, h->n_unk));
-    if (h->fs == RT_FS_DELO_PARABOLIC)
-        RT_TRY(dalloc(&h->d_rpart, (size_t)ray_slots(h) * 2 * acc));
     RT_TRY(h2d(h->d_tau, p->tau, acc));
     RT_TRY(h2d(h->d_B, B.data(), acc));
     RT_TRY(h2d(h->d_opac, p->opac, nphi));
@@ -1033,7 +1033,7 @@ int rt_plan_key(const rt_problem *p, int precision, const char *arch, char *buf,
 
 int rt_sweep_coef_mode(const rt_handle *h, int fp32, int *mode) {
     if (!h || !mode) return fail(RT_EINVAL, "NULL handle or output");
-    *mode = coef_mode_of(h, fp32 != 0);
+    *mode = fp32 ? h->cm32 : h->cm64;
     return RT_OK;
 }
 

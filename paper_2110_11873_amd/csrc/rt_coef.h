@@ -166,6 +166,23 @@ __device__ inline void parabolic_coef(double d, double dd, double &E, double &cu
     cd = (w2 - d * w1) * d * inv;
 }
 
+// The parabolic step's weights in the sweep's form (rt_sweep_kernel.h), for an
+// interval of optical step d and depth step h: w = w0 / d and
+// g = h^2 (2 w1 / d^2 - w0 / d) = (h / d)^2 (w2 - d w1), the second form free of
+// cancellation below d = 1 (w2 ~ d^3 / 3, d w1 ~ d^3 / 2).
+__device__ inline void parabolic_wg(double d, double h, double &w, double &g) {
+    if (d < 1e-100) {  // the limits; d^3 would underflow
+        w = 1.0;
+        g = 0.0;
+        return;
+    }
+    double E, w0, w1, w2;
+    exp_moments(d, E, w0, w1, w2);
+    const double r = h / d;
+    w = w0 / d;
+    g = r * r * (w2 - d * w1);
+}
+
 __device__ inline void ray_step(int fs, double d, double dd, bool has_dn, double &E,
                                 double &cu, double &ck, double &cd) {
     cd = 0.0;

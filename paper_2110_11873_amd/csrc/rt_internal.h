@@ -78,6 +78,9 @@ struct RayConst {
 constexpr int kCoefPairs = 0;
 constexpr int kCoefW = 1;
 constexpr int kCoefRecompute = 2;
+// DELO-parabolic (in FP64, whatever the coefficient mode): (w, g) streamed,
+// the linear step's weight and that of the source's curvature.
+constexpr int kCoefParabolic = 3;
 
 struct SweepArgs {
     const AtmDesc *atm;
@@ -158,8 +161,11 @@ RT_SWEEP_LAUNCHER(launch_sweep_f32_w);
 RT_SWEEP_LAUNCHER(launch_sweep_f64_w);
 RT_SWEEP_LAUNCHER(launch_sweep_f32_rc);
 RT_SWEEP_LAUNCHER(launch_sweep_f64_rc);
+RT_SWEEP_LAUNCHER(launch_sweep_f64_par);
 #undef RT_SWEEP_LAUNCHER
-// The coefficient mode (kCoef*) of a handle's FP32 or FP64 sweeps.
+// The coefficient mode (kCoef*) of a handle's FP32 or FP64 sweeps, and whether
+// a sweep asked for in FP32 runs in it (DELO-parabolic sweeps in FP64 only).
+bool sweeps_fp32(const rt_handle *h, bool fp32);
 int coef_mode_of(const rt_handle *h, bool fp32);
 // Launch configuration of the sweep for a handle: waves per block and whether
 // the next ray batch is loaded during the current one.
@@ -283,7 +289,6 @@ struct rt_handle {
     int plan_status = 0;          // stored launch plan: 0 none, 1 current, 2 other sources
     double *d_partial = nullptr;
     double *d_diag = nullptr, *d_dinv = nullptr, *d_b = nullptr;
-    double *d_rpart = nullptr;    // ray-per-lane sweep: per-wavefront quadrature slots
     int *d_mu_idx = nullptr;      // per |mu| index m: caller's index of -mu (2m) and +mu (2m+1)
     double *d_fsig = nullptr;     // field formulation: J I, 2 values per depth point
     double *d_Rw = nullptr;       // redistribution: R(p, q) w_q per slab, [q][p]
@@ -374,10 +379,6 @@ hipError_t apply_operator_into(rt_handle *h, const double *in, double *out, doub
 hipError_t apply_sweep(rt_handle *h, const double *in, const double *scale, const int *mask,
                        bool fp32, hipStream_t s);
 
-// The operator with the ray-per-lane FP64 sweep (formal solvers with a
-// three-point stencil, rt_raysweep.hip): same contract as apply_operator.
-hipError_t apply_ray_operator(rt_handle *h, const double *in, const double *scale, double *out,
-                              const int *mask, int mode, hipStream_t s);
 // The field as unknown (eq. crd_linear_system2, rt_field.hip): out = (Id -
 // Lambda T J) in; b = Lambda T c + t; sigma = J I (+ c when with_c).
 hipError_t apply_field_operator(rt_handle *h, const double *in, double *out, hipStream_t s);
@@ -420,9 +421,6 @@ hipError_t prd_diag(const rt_handle *h, double *diag, double *dinv, hipStream_t 
 int ensure_prd(rt_handle *h, hipStream_t s);
 int solve_prd_gmres(rt_handle *h, const double *b, double *x, rt_solve_info *info,
                     hipStream_t s);
-// Quadrature slots per slab of that sweep (two per wavefront of rays).
-int ray_slots(const rt_handle *h);
-
 // Destroy the handle's captured solver graphs.
 void clear_graphs(rt_handle *h);
 

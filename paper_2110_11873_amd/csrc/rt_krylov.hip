@@ -1300,7 +1300,7 @@ struct Driver {
 
     // the fused Arnoldi step covers every slab and the restart length
     bool fused() const {
-        return h->ns_max <= NTF && h->ws_restart < MR && h->fs != RT_FS_DELO_PARABOLIC;
+        return h->ns_max <= NTF && h->ws_restart < MR;
     }
 
     // sweep of A P^-1 v_j, then the Arnoldi step (fused or not)
@@ -1314,7 +1314,7 @@ struct Driver {
                 ok(apply_sweep(h, vj, h->d_dinv, h->d_cycle, fp32, s));
             }
             VecArgs af = a;
-            af.part_f32 = fp32 ? 1 : 0;  // the sweep's partial sums are in its precision
+            af.part_f32 = sweeps_fp32(h, fp32) ? 1 : 0;  // the sweep's partial sums are in its precision
             if (j < 16)
                 hipLaunchKernelGGL(gm_arnoldi_fused_kernel<16>, dim3(h->n_atm), dim3(NTF), 0, s, af, j);
             else

@@ -116,8 +116,8 @@ __global__ void ray_setup_kernel(const double *mu_pos, const double *w_pos, int 
 // so a wavefront reads each step as 64 consecutive entries, and the last step
 // only for the chunks that have one.  An entry is the pair (E, w) or w alone
 // (the sweep then derives E = 1 - w d).  Padding (frequencies beyond the
-// last, intervals beyond ns - 2) is E = w = 1: the step leaves I unchanged,
-// and the source beyond the slab is zero.  The rays' quadrature weights and
+// last, intervals beyond ns - 2) is E = w = 1 (DELO-parabolic, whose entries
+// are the pairs (w, g): w = 1, g = 0): the step leaves I unchanged, and the source beyond the slab is zero.  The rays' quadrature weights and
 // (kappa, 1 / kappa) are laid out by slot (q_off + (m*nwb + b)*G + slot),
 // zero for padding rays, so the sweep never masks a loaded value.
 // --------------------------------------------------------------------------
@@ -149,9 +149,15 @@ __global__ void coef_build_kernel(int M, const AtmDesc *atm, const BlockDesc *bl
             if (last && !longc) continue;
             const int j = s0 + i;
             double E = 1.0, w = 1.0;
+            const bool curved = fs == RT_FS_DELO_PARABOLIC;  // (w, g) instead of (E, w)
             if (p < at.n_nu && j < at.ns - 1) {
-                const double d = kap * (tau[at.doff + j + 1] - tau[at.doff + j]);
-                step_ew(fs, d, E, w);
+                const double h = tau[at.doff + j + 1] - tau[at.doff + j], d = kap * h;
+                if (curved)
+                    parabolic_wg(d, h, E, w);
+                else
+                    step_ew(fs, d, E, w);
+            } else if (curved) {
+                w = 0.0;
             }
             const long long e = at.coef_off + ((long long)m * at.nwb + b) * at.bstride +
                                 (last ? (long long)(at.Leff - 1) * kWave + g * at.nlong + c
@@ -394,11 +400,20 @@ hipError_t launch_sweep(int L, int W, bool pf, bool fp32, int cm, const SweepArg
         case kCoefRecompute:
             return fp32 ? launch_sweep_f32_rc(L, W, pf, a, nblocks, ns_max, s)
                         : launch_sweep_f64_rc(L, W, pf, a, nblocks, ns_max, s);
+        case kCoefParabolic:
+            return launch_sweep_f64_par(L, W, pf, a, nblocks, ns_max, s);
     }
     return hipErrorInvalidValue;
 }
 
-int coef_mode_of(const rt_handle *h, bool fp32) { return fp32 ? h->cm32 : h->cm64; }
+bool sweeps_fp32(const rt_handle *h, bool fp32) {
+    return fp32 && h->fs != RT_FS_DELO_PARABOLIC;
+}
+
+int coef_mode_of(const rt_handle *h, bool fp32) {
+    if (h->fs == RT_FS_DELO_PARABOLIC) return kCoefParabolic;
+    return fp32 ? h->cm32 : h->cm64;
+}
 
 hipError_t launch_coef_build(int nblocks, int W, int M, const AtmDesc *atm, const BlockDesc *blk,
                              const double *tau, const double *opac, const double *mu_pos, int fs,

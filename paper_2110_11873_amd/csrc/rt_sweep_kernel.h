@@ -12,8 +12,9 @@
 // per block.  PF: 1 = the next ray batch of a wave is loaded while the
 // current one is computed.  CM: where a step's coefficients (E, w) come from
 // (kCoefPairs: both streamed from the tiles; kCoefW: w streamed, E = 1 - w d
-// derived; kCoefRecompute: both computed from d), d = kappa dtau the optical
-// step of the interval, kappa = r_p / |mu| per ray, dtau per interval.  Each
+// derived; kCoefRecompute: both computed from d; kCoefParabolic: w and the
+// curvature weight g streamed, see process), d = kappa dtau the optical step
+// of the interval, kappa = r_p / |mu| per ray, dtau per interval.  Each
 // block writes the 2 ns quadrature sums of its rays to its own slot of
 // `partial`; the finalize pass adds the slots of a slab in block order and
 // applies sigma_out = z - xi [J00, W2 J20].
@@ -304,8 +305,9 @@ __device__ __forceinline__ void sweep_rays(const SweepArgs &a, const BlockDesc &
                                            const AtmDesc &at, int wave, int lane, T *sacc,
                                            const T *src) {
     using P2 = typename Pair<T>::type;
-    // one tile entry: the (E, w) pair, or w alone
-    using Ent = typename std::conditional<CM == kCoefPairs, P2, T>::type;
+    // one tile entry: the pair (E, w) or (w, g), or w alone
+    using Ent =
+        typename std::conditional<CM == kCoefPairs || CM == kCoefParabolic, P2, T>::type;
     const int ns = at.ns;
     const int c = lane_chunk(lane, C), g = lane_slot(lane, C);
     // the chunk: first depth point s0, len = LE or LE - 1 intervals (a short
@@ -356,6 +358,28 @@ __device__ __forceinline__ void sweep_rays(const SweepArgs &a, const BlockDesc &
             const bool on = i < len && j < ns - 1;
             dt[i] = on ? (T)a.dtau[at.doff + min(j, ns - 2)] : (T)0;
             if constexpr (CM == kCoefRecompute) rdt[i] = on ? (T)1 / dt[i] : (T)0;
+        }
+    }
+
+    // DELO-parabolic: half the second derivative in tau of the parabola
+    // through points k - 1, k, k + 1 (both sources), at the chunk's points;
+    // zero at the slab's ends, where a step into the last point of a ray has
+    // no downwind point and is the linear one
+    constexpr bool kCurved = CM == kCoefParabolic;
+    T cv0[kCurved ? LE + 1 : 1], cv2[kCurved ? LE + 1 : 1];
+    if constexpr (kCurved) {
+#pragma unroll
+        for (int i = 0; i <= LE; ++i) {
+            const int k = s0 + min(i, len);
+            const bool on = k >= 1 && k <= ns - 2;
+            const int kc = on ? k : 1, kp = min(kc + 1, ns - 1);
+            const T ha = (T)a.dtau[at.doff + kc - 1], hb = (T)a.dtau[at.doff + min(kc, ns - 2)];
+            const T ra = (T)1 / ha, rb = (T)1 / hb, rs = (T)1 / (ha + hb);
+            const T x0 = src[2 * kc], x2 = src[2 * kc + 1];
+            const T v0 = ((src[2 * kp] - x0) * rb - (x0 - src[2 * kc - 2]) * ra) * rs;
+            const T v2 = ((src[2 * kp + 1] - x2) * rb - (x2 - src[2 * kc - 1]) * ra) * rs;
+            cv0[i] = on ? v0 : (T)0;
+            cv2[i] = on ? v2 : (T)0;
         }
     }
 
@@ -420,7 +444,7 @@ __device__ __forceinline__ void sweep_rays(const SweepArgs &a, const BlockDesc &
             load_pair(rsrc, voff_last + b * bbytes, 0, cn[LE - 1]);
         }
         qn = load_f64(qrsrc, (b * at.G + g) * 8);
-        if constexpr (CM == kCoefW) kn.x = load_f64(krsrc, (b * at.G + g) * 16);
+        if constexpr (CM == kCoefW || kCurved) kn.x = load_f64(krsrc, (b * at.G + g) * 16);
         if constexpr (CM == kCoefRecompute) kn = load_f64x2(krsrc, (b * at.G + g) * 16);
     };
 
@@ -435,10 +459,15 @@ __device__ __forceinline__ void sweep_rays(const SweepArgs &a, const BlockDesc &
                 ws[i] = cn[i].y;
             }
             if (!longc) Es[LE - 1] = ws[LE - 1] = (T)1;  // zero-length step
-        } else if constexpr (CM == kCoefW) {
+        } else if constexpr (CM == kCoefW || kCurved) {
             const T kap = (T)kd.x;
 #pragma unroll
-            for (int i = 0; i < LE; ++i) ws[i] = cn[i];
+            for (int i = 0; i < LE; ++i) {
+                if constexpr (kCurved)
+                    ws[i] = cn[i].x;
+                else
+                    ws[i] = cn[i];
+            }
             if (!longc) ws[LE - 1] = (T)1;  // zero-length step (its d is 0)
 #pragma unroll
             for (int i = 0; i < LE; ++i) Es[i] = fma(-ws[i], kap * dt[i], (T)1);
@@ -463,19 +492,44 @@ __device__ __forceinline__ void sweep_rays(const SweepArgs &a, const BlockDesc &
         // map D_out = P D_in + (U, V) per direction.  p = w (S_u - S_k) is
         // formed once per step and source and serves both directions and
         // passes; one product of E serves both directions.
-        T p0[LE], p2[LE];
+        //
+        // DELO-parabolic: both directions of a ray see the same parabola at a
+        // point, S + M (tau - tau_k) + C (tau - tau_k)^2, and with the upwind
+        // difference quotient for M the step becomes the linear one plus the
+        // curvature,
+        //   D_k = E D_u + w (S_u - S_k) + C_k g,
+        //   w = w_0 / d,  g = dtau^2 (2 w_1 / d^2 - w_0 / d),
+        //   w_n = int_0^d t^n e^{-t} dt,
+        // so the step's coefficients depend on its own interval only and
+        // serve both directions, as those of the two-point solvers.
+        T p0[LE], p2[LE], m0[kCurved ? LE : 1], m2[kCurved ? LE : 1];
 #pragma unroll
         for (int i = 0; i < LE; ++i) {
             p0[i] = ws[i] * dl0[i];
             p2[i] = ws[i] * dl2[i];
+            if constexpr (kCurved) {
+                const T g = (i + 1 < LE || longc) ? cn[i].y : (T)0;
+                m0[i] = fma(cv0[i], g, -p0[i]);
+                m2[i] = fma(cv2[i], g, -p2[i]);
+                p0[i] = fma(cv0[i + 1], g, p0[i]);
+                p2[i] = fma(cv2[i + 1], g, p2[i]);
+            }
         }
-        T dU = p0[0], dV = p2[0], uU = -p0[LE - 1], uV = -p2[LE - 1], Pd = Es[0];
+        auto up0 = [&](int i) -> T {
+            if constexpr (kCurved) return m0[i];
+            return -p0[i];
+        };
+        auto up2 = [&](int i) -> T {
+            if constexpr (kCurved) return m2[i];
+            return -p2[i];
+        };
+        T dU = p0[0], dV = p2[0], uU = up0(LE - 1), uV = up2(LE - 1), Pd = Es[0];
 #pragma unroll
         for (int i = 1; i < LE; ++i) {
             dU = fma(Es[i], dU, p0[i]);
             dV = fma(Es[i], dV, p2[i]);
-            uU = fma(Es[LE - 1 - i], uU, -p0[LE - 1 - i]);
-            uV = fma(Es[LE - 1 - i], uV, -p2[LE - 1 - i]);
+            uU = fma(Es[LE - 1 - i], uU, up0(LE - 1 - i));
+            uV = fma(Es[LE - 1 - i], uV, up2(LE - 1 - i));
             Pd *= Es[i];
         }
         T Pu = Pd;
@@ -507,8 +561,8 @@ __device__ __forceinline__ void sweep_rays(const SweepArgs &a, const BlockDesc &
             AU[i + 1] = fma(q, xdU, AU[i + 1]);
             AV[i + 1] = fma(q, xdV, AV[i + 1]);
             const int j = LE - 1 - i;
-            xuU = fma(Es[j], xuU, -p0[j]);
-            xuV = fma(Es[j], xuV, -p2[j]);
+            xuU = fma(Es[j], xuU, up0(j));
+            xuV = fma(Es[j], xuV, up2(j));
             AU[j] = fma(q, xuU, AU[j]);
             AV[j] = fma(q, xuV, AV[j]);
         }
@@ -638,14 +692,17 @@ __device__ __forceinline__ void dispatch_le(const SweepArgs &a, const BlockDesc 
     }
 }
 
-// Waves per SIMD the register allocation is held to, for the bodies of chunk
-// length 8 that stream w: 5 in FP32 (96 registers, a handful spilled) and 3
-// in FP64 (168 registers, about 20 spilled; left alone it takes 244 and runs
-// two waves per SIMD, 3-6% slower).  The recomputing bodies would spill more.
+// Waves per SIMD the register allocation is held to.  Chunk length 8, w
+// streamed: 4 in FP32 (96 registers; held to 5 it spilled a handful, 61.6 us
+// against 56.8 for 512 slabs of 64 to 512 points) and 3 in FP64 (168
+// registers, about 20 spilled: 120 us, as with two waves and none spilled).
+// DELO-parabolic: 2 (254 registers at chunk length 8, none spilled).  The
+// recomputing bodies would spill more.
 template <typename T, int L, int CM>
 struct MinWaves {
     static constexpr int value =
-        (L == 8 && CM == kCoefW) ? (sizeof(T) == 4 ? 4 : 3) : 1;
+        L == 8 && CM == kCoefW ? (sizeof(T) == 4 ? 4 : 3)
+                               : (L <= 8 && CM == kCoefParabolic ? 2 : 1);
 };
 
 // LDS: the quadrature rows (a.rows ? W : 1) x 2 ns_max values of type T, then
