@@ -564,7 +564,7 @@ void rt_destroy(rt_handle *h) {
                     h->d_pz,    h->d_ones,  h->d_LU,      h->d_piv,     h->d_sing,
                     h->d_mu_idx, h->d_fsig, h->d_Rw,   h->d_Rw_bf, h->d_prd_Jm,
                     h->d_prd_J, h->d_prd_diag, h->d_prd_dinv, h->d_w64, h->d_w32, h->d_kt,
-                    h->d_dtau, h->seg_ws[0], h->seg_ws[1], h->d_lu_order};
+                    h->d_dtau, h->seg_ws[0], h->seg_ws[1], h->d_lu_order, h->d_perm, h->d_tri_order};
     clear_graphs(h);
     if (h->gstream) (void)hipStreamDestroy(h->gstream);
     for (hipEvent_t e : h->gev)
@@ -892,6 +892,20 @@ int rt_setup(rt_handle **out, const rt_problem *p, const rt_options *o) {
         RT_TRY(dalloc(&h->d_blk_tail, h->n_blocks_tail));
         RT_TRY(h2d(h->d_atm_tail, atm_t.data(), h->n_atm));
         RT_TRY(h2d(h->d_blk_tail, blk_t_h.data(), h->n_blocks_tail));
+    }
+
+    // the triangular solves take a workgroup per slab, two of them per CU at
+    // a time: largest first, every other run of 256 (one per CU) reversed, so
+    // that a CU's slabs add up to similar sizes
+    {
+        std::vector<int> order(h->n_atm);
+        std::iota(order.begin(), order.end(), 0);
+        std::stable_sort(order.begin(), order.end(),
+                         [&](int x, int y) { return h->ns[x] > h->ns[y]; });
+        for (size_t i = 256; i < order.size(); i += 512)
+            std::reverse(order.begin() + i, order.begin() + std::min(i + 256, order.size()));
+        RT_TRY(dalloc(&h->d_tri_order, h->n_atm));
+        RT_TRY(h2d(h->d_tri_order, order.data(), h->n_atm));
     }
 
     // ---- precompute: ray constants, tile coefficients, D and D^-1, b

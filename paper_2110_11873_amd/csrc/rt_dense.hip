@@ -6,11 +6,8 @@
 //   SOR   P = omega^-1 D + U,
 //   SSOR  P = omega (2 - omega)^-1 (omega^-1 D + U) D^-1 (omega^-1 D + L).
 // One workgroup per slab keeps the slab's vector (at most 2 RT_MAX_NS values)
-// in LDS and walks the triangle in blocks of 64 unknowns: the block's
-// diagonal 64 x 64 part is staged in LDS and solved by one wavefront, the
-// solved values are broadcast with readlane, and the rows still to come are
-// updated with the block's columns (16 lanes per row, each row's 64 entries
-// read once, contiguously).  Each triangle of A is read from memory once.
+// in LDS and substitutes in blocks of 64 unknowns (tri_sweep).  Each triangle
+// of A is read from memory once.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -21,10 +18,14 @@ namespace rt {
 
 namespace {
 
-constexpr int kTriNT = 256;
-constexpr int kTriPass = 4;  // 16-row passes of the update loaded together
-constexpr int kTriB = 64;
-constexpr int kTriPad = kTriB + 1;  // padded row of the staged block
+constexpr int kTriNT = 512;                 // 8 wavefronts of 8 rows of a block each
+constexpr int kTriWaves = kTriNT / kWave;
+constexpr int kTriB = 64;                   // unknowns per block
+constexpr int kTriRows = kTriB / kTriWaves;  // rows of a block per wavefront
+constexpr int kTriPad = 2 * kTriB + 1;      // padded row of the staged columns
+// LDS: the staged 64 x 128 columns, the two buffers of row sums, the vector
+constexpr int kTriHead = kTriB * kTriPad + 2 * kTriB;
+static_assert(kTriRows == 8 && kTriHead % 2 == 0, "8 row sums reduced; the vector 16-byte aligned");
 
 __device__ inline double readlane_d(double v, int lane) {
     const long long b = __double_as_longlong(v);
@@ -36,133 +37,134 @@ __device__ inline double readlane_d(double v, int lane) {
 // r <- (omega^-1 D + T)^-1 r for T the strict upper (UP) or lower triangle
 // of the slab's A (row-major, N x N), r in LDS; UNIT: a unit diagonal instead
 // of omega^-1 D (the L factor of an LU factorization).
-template <bool UP, bool UNIT = false, bool ROWWISE = false>
-__device__ void tri_sweep(const double *A, int N, double om, double *r, double *blk) {
-    const int tid = threadIdx.x;
+//
+// Blocks of 64 unknowns, in the order of substitution.  At step t one
+// wavefront finishes block t -- the product with the 64 columns solved at step
+// t - 1 and the block's own triangle, both staged in LDS, one row per lane --
+// while all of them add up block t + 1's rows times every column solved
+// before step t.  So only the 128 staged columns wait for a solution: the rest
+// of the triangle streams from memory with nothing in the way, each row a
+// contiguous run, 8 rows in flight per wavefront.  What bounds it is that
+// stream: 512 slabs of 128 to 1024 unknowns, both triangles (1.7 GB), take 358
+// us, 4.8 TB/s, a copy on this card reaching 5.1; updating every row still to
+// come after each block, whose loads wait for the block, took 904 us.
+template <bool UP, bool UNIT = false>
+__device__ __forceinline__ void tri_sweep(const double *A, int N, double om, double *r, double *blk,
+                                          double *part) {
+    const int tid = threadIdx.x, lane = tid % kWave;
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int nb = (N + kTriB - 1) / kTriB;
-    constexpr int kStage = kTriB * kTriB / kTriNT;
-    // a block's diagonal part, loaded into registers (all loads in flight
-    // together); the next block's is loaded before this block's update
-    auto load_diag = [&](int b, double *stage) {
-        const int i0 = b * kTriB, n = min(kTriB, N - i0);
+    // first unknown of the block of step t, and its first staged column: the
+    // block's own 64 and the 64 of step t - 1 beside them
+    auto first = [&](int t) { return kTriB * (UP ? nb - 1 - t : t); };
+    auto col0 = [&](int t) { return UP ? first(t) : first(t) - kTriB; };
+    constexpr int kStage = kTriB * kTriB / kTriNT;  // column pairs per thread
+    auto load_blk = [&](int t, double2 (&st)[kStage]) {
+        const int i0 = first(t), c = col0(t) + 2 * lane;  // pairs: N and c are even
 #pragma unroll
-        for (int t = 0; t < kStage; ++t) {
-            const int e = tid + t * kTriNT, rr = e / kTriB, cc = e % kTriB;
-            stage[t] = (rr < n && cc < n) ? A[(long long)(i0 + rr) * N + i0 + cc] : 0.0;
+        for (int u = 0; u < kStage; ++u) {
+            const int row = i0 + wave + kTriWaves * u;
+            st[u] = make_double2(0.0, 0.0);
+            if (row < N && c >= 0 && c < N)
+                st[u] = *reinterpret_cast<const double2 *>(A + (long long)row * N + c);
         }
     };
-    double stage[kStage];
-    if constexpr (!ROWWISE) load_diag(UP ? nb - 1 : 0, stage);
-    for (int bi = 0; bi < nb; ++bi) {
-        const int b = UP ? nb - 1 - bi : bi;
-        const int i0 = b * kTriB, n = min(kTriB, N - i0);
-        if constexpr (ROWWISE) load_diag(b, stage);  // no registers to spare during the update
-#pragma unroll
-        for (int t = 0; t < kStage; ++t) {
-            const int e = tid + t * kTriNT;
-            blk[(e / kTriB) * kTriPad + e % kTriB] = stage[t];
+    auto solve = [&](int t) {
+        const int c = lane, i0 = first(t), own = UP ? 0 : kTriB, side = kTriB - own;
+        const double *row = blk + c * kTriPad;
+        double val = i0 + c < N ? r[i0 + c] - part[(t & 1) * kTriB + c] : 0.0;
+        if (t > 0) {
+            const double *x = r + first(t - 1);
+            const int n = min(kTriB, N - first(t - 1));
+            double s0 = 0.0, s1 = 0.0;
+#pragma unroll 8
+            for (int i = 0; i < n; i += 2) {
+                s0 = fma(row[side + i], x[i], s0);
+                s1 = fma(row[side + i + 1], x[i + 1], s1);
+            }
+            val -= s0 + s1;
         }
-        __syncthreads();
-        if constexpr (!ROWWISE)
-            if (bi + 1 < nb) load_diag(UP ? b - 1 : b + 1, stage);
-        if (tid < kWave) {
-            const int c = tid;
-            double val = c < n ? r[i0 + c] : 0.0;
-            const double dc = c < n ? (UNIT ? 1.0 : om / blk[c * kTriPad + c]) : 0.0;
-            if (n == kTriB) {
-                // a full block: eight steps at a time, their LDS reads issued first
-                // (the outer loop stays rolled: one group's reads in registers)
+        // rows scaled by the inverse diagonal, so a step is one broadcast and
+        // one multiply-add; columns outside the triangle count as zero
+        const double dc = UNIT ? 1.0 : i0 + c < N ? om / row[own + c] : 0.0;
+        val *= dc;
 #pragma unroll 1
-                for (int i8 = 0; i8 < kTriB; i8 += 8) {
-                    double col[8];
+        for (int i8 = 0; i8 < kTriB; i8 += 8) {
+            double col[8];
 #pragma unroll
-                    for (int u = 0; u < 8; ++u) {
-                        const int i = UP ? kTriB - 1 - (i8 + u) : i8 + u;
-                        col[u] = blk[c * kTriPad + i];
-                    }
-#pragma unroll
-                    for (int u = 0; u < 8; ++u) {
-                        const int i = UP ? kTriB - 1 - (i8 + u) : i8 + u;
-                        const double zi = readlane_d(val * dc, i);
-                        if (c == i) val = zi;
-                        else if (UP ? c < i : c > i) val -= col[u] * zi;
-                    }
-                }
-            } else {
-                for (int ii = 0; ii < n; ++ii) {
-                    const int i = UP ? n - 1 - ii : ii;
-                    const double zi = readlane_d(val * dc, i);
-                    if (c == i) val = zi;
-                    else if (UP ? c < i : c > i) val -= blk[c * kTriPad + i] * zi;
-                }
+            for (int u = 0; u < 8; ++u) {
+                const int i = UP ? kTriB - 1 - (i8 + u) : i8 + u;
+                const double e = UNIT ? row[own + i] : row[own + i] * dc;
+                col[u] = (UP ? c < i : c > i) ? e : 0.0;
             }
-            if (c < n) r[i0 + c] = val;
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const int i = UP ? kTriB - 1 - (i8 + u) : i8 + u;
+                val = fma(-col[u], readlane_d(val, i), val);
+            }
         }
+        if (i0 + c < N) r[i0 + c] = val;
+    };
+    // part <- the rows of step t + 1's block times the columns solved before step t
+    auto stream = [&](int t) {
+        const int lo = UP ? first(t - 1) : 0, hi = UP ? N : first(t);
+        const int row0 = first(t + 1) + kTriRows * wave;
+        const double *p[kTriRows];
+        double acc[kTriRows];
+#pragma unroll
+        for (int q = 0; q < kTriRows; ++q) {
+            p[q] = A + (long long)min(row0 + q, N - 1) * N;
+            acc[q] = 0.0;
+        }
+#pragma unroll 2
+        for (int c = lo + 2 * lane; c < hi; c += 2 * kWave) {
+            const double2 x = *reinterpret_cast<const double2 *>(r + c);
+            double2 v[kTriRows];
+#pragma unroll
+            for (int q = 0; q < kTriRows; ++q) v[q] = *reinterpret_cast<const double2 *>(p[q] + c);
+#pragma unroll
+            for (int q = 0; q < kTriRows; ++q) acc[q] = fma(v[q].x, x.x, fma(v[q].y, x.y, acc[q]));
+        }
+        // the 8 sums over the wavefront: halves exchanged (rows 4-7 in the upper
+        // 32 lanes, then pairs, then single rows), then added within 8 lanes
+        double h4[4], h2[2], h;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const bool up = lane & 32;
+            const double mine = up ? acc[q + 4] : acc[q], other = up ? acc[q] : acc[q + 4];
+            h4[q] = mine + __shfl_xor(other, 32);
+        }
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const bool up = lane & 16;
+            const double mine = up ? h4[q + 2] : h4[q], other = up ? h4[q] : h4[q + 2];
+            h2[q] = mine + __shfl_xor(other, 16);
+        }
+        {
+            const bool up = lane & 8;
+            const double mine = up ? h2[1] : h2[0], other = up ? h2[0] : h2[1];
+            h = mine + __shfl_xor(other, 8);
+        }
+        for (int off = 4; off > 0; off >>= 1) h += __shfl_xor(h, off);
+        if ((lane & 7) == 0) {
+            const int q = (lane & 32 ? 4 : 0) + (lane & 16 ? 2 : 0) + (lane & 8 ? 1 : 0);
+            part[((t + 1) & 1) * kTriB + kTriRows * wave + q] = h;
+        }
+    };
+    double2 st[kStage];
+    load_blk(0, st);
+    if (tid < 2 * kTriB) part[tid] = 0.0;
+    for (int t = 0; t < nb; ++t) {
+#pragma unroll
+        for (int u = 0; u < kStage; ++u) {
+            double *to = blk + (wave + kTriWaves * u) * kTriPad + 2 * lane;
+            to[0] = st[u].x;
+            to[1] = st[u].y;
+        }
+        if (t + 1 < nb) load_blk(t + 1, st);
         __syncthreads();
-        const int lo = UP ? 0 : i0 + n, hi = UP ? i0 : N;
-        if constexpr (ROWWISE) {
-            // one thread per row, each row's 64 entries loaded together: the
-            // most bytes in flight per thread (a lone large slab)
-            for (int l = lo + tid; l < hi; l += kTriNT) {
-                const double2 *row = reinterpret_cast<const double2 *>(A + (long long)l * N + i0);
-                double acc0 = 0.0, acc1 = 0.0;
-                if (n == kTriB) {
-                    double2 v[kTriB / 2];
-#pragma unroll
-                    for (int c2 = 0; c2 < kTriB / 2; ++c2) v[c2] = row[c2];
-#pragma unroll
-                    for (int c2 = 0; c2 < kTriB / 2; ++c2) {
-                        acc0 = fma(v[c2].x, r[i0 + 2 * c2], acc0);
-                        acc1 = fma(v[c2].y, r[i0 + 2 * c2 + 1], acc1);
-                    }
-                } else {
-                    for (int c2 = 0; c2 < n / 2; ++c2) {
-                        const double2 v = row[c2];
-                        acc0 = fma(v.x, r[i0 + 2 * c2], acc0);
-                        acc1 = fma(v.y, r[i0 + 2 * c2 + 1], acc1);
-                    }
-                }
-                r[l] -= acc0 + acc1;
-            }
-        } else {
-            // the rows not yet solved (above the block for UP, else below) less
-            // the block's columns times its solution: thread (row q, group g)
-            // takes columns 4g .. 4g + 3, so each row's 64 entries are read by 16
-            // neighbouring lanes (512 contiguous bytes), and the 16 partial sums
-            // are added by butterfly; kTriPass passes of kTriNT / 16 rows each
-            // are loaded together
-            const int q = tid >> 4, g = tid & 15, c0 = 4 * g;
-            double x[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) x[u] = c0 + u < n ? r[i0 + c0 + u] : 0.0;
-            for (int l0 = lo; l0 < hi; l0 += kTriPass * (kTriNT / 16)) {
-                double acc[kTriPass];
-#pragma unroll
-                for (int pass = 0; pass < kTriPass; ++pass) {
-                    const int l = l0 + pass * (kTriNT / 16) + q;
-                    acc[pass] = 0.0;
-                    if (l < hi) {
-                        const double *row = A + (long long)l * N + i0 + c0;
-                        if (c0 + 3 < n) {
-                            const double2 v0 = reinterpret_cast<const double2 *>(row)[0];
-                            const double2 v1 = reinterpret_cast<const double2 *>(row)[1];
-                            acc[pass] = fma(v0.x, x[0], fma(v0.y, x[1], fma(v1.x, x[2], v1.y * x[3])));
-                        } else {
-#pragma unroll
-                            for (int u = 0; u < 4; ++u)
-                                if (c0 + u < n) acc[pass] = fma(row[u], x[u], acc[pass]);
-                        }
-                    }
-                }
-#pragma unroll
-                for (int pass = 0; pass < kTriPass; ++pass) {
-                    double v = acc[pass];
-                    for (int off = 8; off > 0; off >>= 1) v += __shfl_xor(v, off);
-                    const int l = l0 + pass * (kTriNT / 16) + q;
-                    if (g == 0 && l < hi) r[l] -= v;
-                }
-            }
-        }
+        if (wave == t % kTriWaves) solve(t);
+        if (t >= 1 && t + 1 < nb) stream(t);
         __syncthreads();
     }
 }
@@ -173,29 +175,29 @@ struct TriArgs {
     const double *in;
     double *out;
     const int *mask;     // optional per-slab activity mask
+    const int *order;    // workgroup -> slab
     double omega;
     int kind;            // RT_PC_SOR or RT_PC_SSOR
 };
 
 // out = P^-1 in.
-template <bool ROWWISE>
-__global__ __launch_bounds__(kTriNT) void tri_solve_kernel(TriArgs a) {
+__global__ __launch_bounds__(kTriNT) __attribute__((amdgpu_waves_per_eu(4, 8))) void tri_solve_kernel(TriArgs a) {
     extern __shared__ double sm[];
-    const int s = blockIdx.x;
+    const int s = a.order[blockIdx.x];
     if (a.mask && a.mask[s] == 0) return;
     const AtmDesc at = a.atm[s];
     const int N = 2 * at.ns;
     const double *A = a.A + at.a_off;
     const long long v0 = 2LL * at.doff;
-    double *blk = sm;                  // [64][65]
-    double *r = sm + kTriB * kTriPad;  // [N]
+    double *blk = sm, *part = sm + kTriB * kTriPad;
+    double *r = sm + kTriHead;  // [N]
     for (int i = threadIdx.x; i < N; i += kTriNT) r[i] = a.in[v0 + i];
     __syncthreads();
-    tri_sweep<true, false, ROWWISE>(A, N, a.omega, r, blk);
+    tri_sweep<true>(A, N, a.omega, r, blk, part);
     if (a.kind == RT_PC_SSOR) {
         for (int i = threadIdx.x; i < N; i += kTriNT) r[i] *= A[(long long)i * N + i];
         __syncthreads();
-        tri_sweep<false, false, ROWWISE>(A, N, a.omega, r, blk);
+        tri_sweep<false>(A, N, a.omega, r, blk, part);
         const double sc = (2.0 - a.omega) / a.omega;
         for (int i = threadIdx.x; i < N; i += kTriNT) r[i] *= sc;
     }
@@ -657,38 +659,48 @@ __global__ __launch_bounds__(256) void lu_rank32_kernel(LuArgs g, int K0) {
     }
 }
 
-// x = A^-1 b from the factors: row exchanges, L y = P b, U x = y.
-template <bool ROWWISE>
-__global__ __launch_bounds__(kTriNT) void lu_solve_kernel(const AtmDesc *atm, const double *LU,
-                                                          const int *pivs, const double *b,
-                                                          double *x) {
-    extern __shared__ double sm[];
-    const int s = blockIdx.x;
-    const AtmDesc at = atm[s];
+// perm[i] = the row of b that the exchanges piv bring to row i.
+__global__ __launch_bounds__(256) void lu_perm_kernel(const AtmDesc *atm, const int *pivs,
+                                                      int *perm) {
+    extern __shared__ int pm[];  // [N] exchanges, [N] rows
+    const AtmDesc at = atm[blockIdx.x];
     const int N = 2 * at.ns;
-    const double *A = LU + at.a_off;
-    const int *piv = pivs + 2LL * at.doff;
     const long long v0 = 2LL * at.doff;
-    double *blk = sm;
-    double *r = sm + kTriB * kTriPad;
-    for (int i = threadIdx.x; i < N; i += kTriNT) r[i] = b[v0 + i];
+    for (int i = threadIdx.x; i < N; i += 256) {
+        pm[i] = pivs[v0 + i];
+        pm[N + i] = i;
+    }
     __syncthreads();
     if (threadIdx.x == 0)
         for (int k = 0; k < N; ++k) {
-            const int p = piv[k];
-            if (p != k) {
-                const double t = r[k];
-                r[k] = r[p];
-                r[p] = t;
-            }
+            const int p = pm[k], t = pm[N + k];
+            pm[N + k] = pm[N + p];
+            pm[N + p] = t;
         }
     __syncthreads();
-    tri_sweep<false, true, ROWWISE>(A, N, 1.0, r, blk);
-    tri_sweep<true, false, ROWWISE>(A, N, 1.0, r, blk);
+    for (int i = threadIdx.x; i < N; i += 256) perm[v0 + i] = pm[N + i];
+}
+
+// x = A^-1 b from the factors: row exchanges, L y = P b, U x = y.
+__global__ __launch_bounds__(kTriNT) __attribute__((amdgpu_waves_per_eu(4, 8))) void lu_solve_kernel(const AtmDesc *atm, const int *order,
+                                                          const double *LU, const int *perm,
+                                                          const double *b, double *x) {
+    extern __shared__ double sm[];
+    const int s = order[blockIdx.x];
+    const AtmDesc at = atm[s];
+    const int N = 2 * at.ns;
+    const double *A = LU + at.a_off;
+    const long long v0 = 2LL * at.doff;
+    double *blk = sm, *part = sm + kTriB * kTriPad;
+    double *r = sm + kTriHead;
+    for (int i = threadIdx.x; i < N; i += kTriNT) r[i] = b[v0 + perm[v0 + i]];
+    __syncthreads();
+    tri_sweep<false, true>(A, N, 1.0, r, blk, part);
+    tri_sweep<true>(A, N, 1.0, r, blk, part);
     for (int i = threadIdx.x; i < N; i += kTriNT) x[v0 + i] = r[i];
 }
 
-size_t tri_lds(int ns_max) { return (size_t)(kTriB * kTriPad + 2 * ns_max) * sizeof(double); }
+size_t tri_lds(int ns_max) { return (size_t)(kTriHead + 2 * ns_max) * sizeof(double); }
 
 template <typename K>
 hipError_t lds_limit(K kernel, size_t lds) {
@@ -704,31 +716,21 @@ TriArgs tri_args(const rt_handle *h, const double *in, double *out, const int *m
     a.in = in;
     a.out = out;
     a.mask = mask;
+    a.order = h->d_tri_order;
     a.omega = h->opt.omega;
     a.kind = h->opt.precond;
     return a;
 }
-
-// Few slabs (fewer workgroups than CUs): each workgroup's own loads in flight
-// decide its speed, so one thread per row with the row's 64 entries loaded
-// together; many slabs: the coalesced 16-lanes-per-row update.
-bool tri_rowwise(const rt_handle *h) { return h->n_atm < 256; }
 
 }  // namespace
 
 hipError_t precond_tri(const rt_handle *h, const double *in, double *out, const int *mask,
                        hipStream_t s) {
     const size_t lds = tri_lds(h->ns_max);
-    const TriArgs a = tri_args(h, in, out, mask);
-    if (tri_rowwise(h)) {
-        hipError_t e = lds_limit(tri_solve_kernel<true>, lds);
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(tri_solve_kernel<true>, dim3(h->n_atm), dim3(kTriNT), lds, s, a);
-    } else {
-        hipError_t e = lds_limit(tri_solve_kernel<false>, lds);
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(tri_solve_kernel<false>, dim3(h->n_atm), dim3(kTriNT), lds, s, a);
-    }
+    const hipError_t e = lds_limit(tri_solve_kernel, lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(tri_solve_kernel, dim3(h->n_atm), dim3(kTriNT), lds, s,
+                       tri_args(h, in, out, mask));
     return hipGetLastError();
 }
 
@@ -753,15 +755,16 @@ int lu_factor(rt_handle *h, hipStream_t s) {
         return fail(RT_EINVAL, "the LU route supports the two-point formal solvers only");
     const size_t bytes = sizeof(double) * (size_t)std::max<long long>(h->n_dense, 1);
     if (!h->d_LU) {
-        // all four or none: a failed allocation frees the others, so a later
+        // all or none: a failed allocation frees the others, so a later
         // call starts over instead of finding a partial set
         if (hipMalloc((void **)&h->d_LU, bytes) != hipSuccess ||
             hipMalloc((void **)&h->d_piv, sizeof(int) * h->n_unk) != hipSuccess ||
+            hipMalloc((void **)&h->d_perm, sizeof(int) * h->n_unk) != hipSuccess ||
             hipMalloc((void **)&h->d_sing, sizeof(int) * h->n_atm) != hipSuccess ||
             hipMalloc((void **)&h->d_lu_order, sizeof(int) * h->n_atm) != hipSuccess) {
             (void)hipGetLastError();
-            for (void **p : {(void **)&h->d_LU, (void **)&h->d_piv, (void **)&h->d_sing,
-                             (void **)&h->d_lu_order}) {
+            for (void **p : {(void **)&h->d_LU, (void **)&h->d_piv, (void **)&h->d_perm,
+                             (void **)&h->d_sing, (void **)&h->d_lu_order}) {
                 if (*p) (void)hipFree(*p);
                 *p = nullptr;
             }
@@ -787,6 +790,15 @@ int lu_factor(rt_handle *h, hipStream_t s) {
         return fail(RT_EDEVICE, "copy of the assembled operator failed");
     LuArgs g{h->d_atm, h->d_LU, h->d_piv, h->d_sing, nullptr};
     const int N = 2 * h->ns_max;
+    // the exchanges as a row order, once: in the solve, one thread walking
+    // them cost about half of it (512 slabs, 1007 us)
+    auto row_order = [&]() -> int {
+        hipLaunchKernelGGL(lu_perm_kernel, dim3(h->n_atm), dim3(256), 2 * N * sizeof(int), s,
+                           (const AtmDesc *)h->d_atm, (const int *)h->d_piv, h->d_perm);
+        if (hipGetLastError() != hipSuccess) return fail(RT_EDEVICE, "LU row order launch failed");
+        h->lu_ready = true;
+        return RT_OK;
+    };
     if (h->n_atm <= kLuSplitSlabs && N > kLuBB) {
         // few slabs: each 32-column block factored by one workgroup per slab,
         // the rest of the matrix updated by workgroups over column and row tiles
@@ -808,8 +820,7 @@ int lu_factor(rt_handle *h, hipStream_t s) {
                                    dim3(256), 0, s, g, K0);
             if (hipGetLastError() != hipSuccess) return fail(RT_EDEVICE, "LU factorization launch failed");
         }
-        h->lu_ready = true;
-        return RT_OK;
+        return row_order();
     }
     g.order = h->d_lu_order;
     // one workgroup per slab with 64-column outer blocks; their U12 stage
@@ -830,26 +841,16 @@ int lu_factor(rt_handle *h, hipStream_t s) {
     else
         launch(lu_factor_kernel<8, kLuNB, false, kLuBBBatch>);
     if (hipGetLastError() != hipSuccess) return fail(RT_EDEVICE, "LU factorization launch failed");
-    h->lu_ready = true;
-    return RT_OK;
+    return row_order();
 }
 
 hipError_t lu_solve(const rt_handle *h, const double *b, double *x, hipStream_t s) {
     const size_t lds = tri_lds(h->ns_max);
-    const AtmDesc *atm = h->d_atm;
-    const double *LU = h->d_LU;
-    const int *piv = h->d_piv;
-    if (tri_rowwise(h)) {
-        hipError_t e = lds_limit(lu_solve_kernel<true>, lds);
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(lu_solve_kernel<true>, dim3(h->n_atm), dim3(kTriNT), lds, s, atm, LU, piv,
-                           b, x);
-    } else {
-        hipError_t e = lds_limit(lu_solve_kernel<false>, lds);
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(lu_solve_kernel<false>, dim3(h->n_atm), dim3(kTriNT), lds, s, atm, LU,
-                           piv, b, x);
-    }
+    const hipError_t e = lds_limit(lu_solve_kernel, lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(lu_solve_kernel, dim3(h->n_atm), dim3(kTriNT), lds, s,
+                       (const AtmDesc *)h->d_atm, (const int *)h->d_tri_order,
+                       (const double *)h->d_LU, (const int *)h->d_perm, b, x);
     return hipGetLastError();
 }
 

@@ -315,6 +315,8 @@ struct rt_handle {
     double *d_ones = nullptr;     // unit diagonal scaling of the Krylov updates
     double *d_LU = nullptr;       // LU factors of the assembled A
     int *d_piv = nullptr;         // their row exchanges
+    int *d_perm = nullptr;        // the exchanges as a row order
+    int *d_tri_order = nullptr;   // workgroup -> slab of the triangular solves
     int *d_sing = nullptr;        // per slab: a zero pivot was met
     int *d_lu_order = nullptr;    // slabs by decreasing size: the factorization's workgroup order
     bool lu_ready = false;
