@@ -560,7 +560,8 @@ void rt_destroy(rt_handle *h) {
                     h->d_V,     h->d_H,     h->d_cs,      h->d_sn,      h->d_g,      h->d_w,
                     h->d_r,     h->d_rh,    h->d_p,       h->d_v,       h->d_s,      h->d_t,
                     h->d_cq,    h->d_state, h->d_active,  h->d_cycle,   h->d_count,
-                    h->d_ew,    h->d_asm_dg, h->d_asm_sc, h->d_asm_task, h->d_A,
+                    h->d_ew,    h->d_asm_dg, h->d_asm_sc, h->d_asm_task, h->d_asm_xt,
+                    h->d_asm_tt, h->d_asm_tile0, h->d_A,
                     h->d_pz,    h->d_ones,  h->d_LU,      h->d_piv,     h->d_sing,
                     h->d_mu_idx, h->d_fsig, h->d_Rw,   h->d_Rw_bf, h->d_prd_Jm,
                     h->d_prd_J, h->d_prd_diag, h->d_prd_dinv, h->d_w64, h->d_w32, h->d_kt,

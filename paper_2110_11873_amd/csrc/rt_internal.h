@@ -305,6 +305,8 @@ struct rt_handle {
 
     // dense route (allocated on first use)
     double2 *d_ew = nullptr;      // (E, w) per slab, interval and ray
+    double *d_asm_xt = nullptr, *d_asm_tt = nullptr;  // transmissions within tiles of 16 depths
+    long long *d_asm_tile0 = nullptr;  // tiles of the slabs before each slab
     double *d_asm_dg = nullptr;   // node-diagonal moments per slice and direction
     double *d_asm_sc = nullptr;   // raw moments of ray slices after the first
     void *d_asm_task = nullptr;   // assembly task list
