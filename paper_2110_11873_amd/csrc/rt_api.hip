@@ -838,7 +838,7 @@ int rt_setup(rt_handle **out, const rt_problem *p, const rt_options *o) {
     RT_TRY(dalloc(&h->d_opac, nphi));
     RT_TRY(dalloc(&h->d_phi, nphi));
     RT_TRY(dalloc(&h->d_mu_pos, h->M));
-    RT_TRY(dalloc(&h->d_mu_idx, (size_t)2 * h->M));
+    RT_TRY(dalloc(&h->d_mu_idx, (size_t)2 * h->n_mu));
     RT_TRY(dalloc(&h->d_fsig, (size_t)2 * acc));
     RT_TRY(dalloc(&h->d_w_pos, h->M));
     RT_TRY(dalloc(&h->d_w_nu, h->n_nu));
@@ -879,7 +879,10 @@ int rt_setup(rt_handle **out, const rt_problem *p, const rt_options *o) {
     RT_TRY(h2d(h->d_opac, p->opac, nphi));
     RT_TRY(h2d(h->d_phi, p->phi, nphi));
     RT_TRY(h2d(h->d_mu_pos, mu_pos.data(), h->M));
-    RT_TRY(h2d(h->d_mu_idx, mu_index.data(), (size_t)2 * h->M));
+    mu_index.resize(2 * (size_t)h->n_mu);  // and back: the |mu| of each index of the caller's
+    for (int m = 0; m < h->M; ++m)
+        mu_index[h->n_mu + mu_index[2 * m]] = mu_index[h->n_mu + mu_index[2 * m + 1]] = m;
+    RT_TRY(h2d(h->d_mu_idx, mu_index.data(), (size_t)2 * h->n_mu));
     RT_TRY(h2d(h->d_w_pos, w_pos.data(), h->M));
     RT_TRY(h2d(h->d_w_nu, p->w_nu, h->n_nu));
     RT_TRY(h2d(h->d_wphi, wphi.data(), nphi));

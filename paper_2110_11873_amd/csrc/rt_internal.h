@@ -289,7 +289,8 @@ struct rt_handle {
     int plan_status = 0;          // stored launch plan: 0 none, 1 current, 2 other sources
     double *d_partial = nullptr;
     double *d_diag = nullptr, *d_dinv = nullptr, *d_b = nullptr;
-    int *d_mu_idx = nullptr;      // per |mu| index m: caller's index of -mu (2m) and +mu (2m+1)
+    int *d_mu_idx = nullptr;      // per |mu| index m: caller's index of -mu (2m) and +mu (2m+1);
+                                  // then, per caller's index, m
     double *d_fsig = nullptr;     // field formulation: J I, 2 values per depth point
     double *d_Rw = nullptr;       // redistribution: R(p, q) w_q per slab, [q][p]
     unsigned short *d_Rw_bf = nullptr;  // R w split in bf16 hi, lo: [2][slab][p][prd_nqp]
