@@ -564,7 +564,7 @@ void rt_destroy(rt_handle *h) {
                     h->d_asm_tt, h->d_asm_tile0, h->d_A,
                     h->d_pz,    h->d_ones,  h->d_LU,      h->d_piv,     h->d_sing,
                     h->d_mu_idx, h->d_fsig, h->d_Rw,   h->d_Rw_bf, h->d_prd_Jm,
-                    h->d_prd_J, h->d_prd_diag, h->d_prd_dinv, h->d_w64, h->d_w32, h->d_kt,
+                    h->d_prd_J, h->d_prd_cuk, h->d_prd_diag, h->d_prd_dinv, h->d_w64, h->d_w32, h->d_kt,
                     h->d_dtau, h->seg_ws[0], h->seg_ws[1], h->d_lu_order, h->d_perm, h->d_tri_order};
     clear_graphs(h);
     if (h->gstream) (void)hipStreamDestroy(h->gstream);
@@ -1115,6 +1115,7 @@ int rt_set_redistribution(rt_handle *h, const double *R) {
     const long long n = (long long)h->n_atm * h->n_nu * h->n_nu;
     for (long long e = 0; e < n; ++e)
         if (!std::isfinite(R[e])) return fail(RT_EINVAL, "R must be finite");
+    if (const int rc = prd_table(h)) return rc;
     // R(p, q) w_q stored transposed ([slab][q][p]), the form the contraction reads
     const int nnu = h->n_nu;
     std::vector<double> w_nu(nnu), Rw(n);

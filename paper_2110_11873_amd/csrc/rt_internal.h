@@ -297,6 +297,7 @@ struct rt_handle {
     int prd_nqp = 0;              // padded row length of the bf16 split (multiple of 32)
     double *d_prd_Jm = nullptr;   // per-|mu| quadrature stage (when not in LDS)
     double *d_prd_J = nullptr;    // monochromatic J, frequency-major [p][k][K]
+    double *d_prd_cuk = nullptr;  // (c_u, c_k) per interval and ray, or NULL
     double *d_prd_diag = nullptr, *d_prd_dinv = nullptr;
     bool prd_ready = false;
     int prd_cached_nt = 0;        // threads of the cached-coefficient sweep, 0: the general sweep
@@ -424,6 +425,7 @@ hipError_t apply_prd_operator(const rt_handle *h, const double *in, double *out,
                               bool bf16x3 = false, const double *scale = nullptr);
 hipError_t prd_diag(const rt_handle *h, double *diag, double *dinv, hipStream_t s);
 int ensure_prd(rt_handle *h, hipStream_t s);
+int prd_table(rt_handle *h);  // its coefficient table, once per handle
 int solve_prd_gmres(rt_handle *h, const double *b, double *x, rt_solve_info *info,
                     hipStream_t s);
 // Destroy the handle's captured solver graphs.

@@ -47,6 +47,7 @@ namespace {
 constexpr int kPrdNT = 256;       // contraction
 constexpr int kPrdSweepNT = 512;  // sweep: lanes per (|mu|, chunk)
 constexpr size_t kPrdLdsMax = 64 * 1024;
+constexpr long long kPrdTableRows = 8LL << 20;  // 16 bytes each: 128 MiB
 typedef double v4d __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef unsigned short u16x8 __attribute__((ext_vector_type(8)));
@@ -66,6 +67,7 @@ struct PrdArgs {
     double *sig_out;
     double *stage;        // global stage (when the LDS one does not fit)
     double *J;            // [n_nu][ns_total][2]
+    const double2 *cuk;   // (c_u, c_k) of every interval and ray: prd_cuk, or NULL
     int fs, M, n_nu, ns_total, ns_max, nch;
 };
 
@@ -252,16 +254,44 @@ __global__ __launch_bounds__(kPrdSweepNT) void prd_sweep_kernel(PrdArgs a) {
 // lane holds at most LMAX points; the host launches this kernel only when
 // every chunk fits.  LDS (doubles): stage [ns_max][M][2], maps
 // [2][nch][M][3], sources [ns_max][2], depths [ns_max].
+//
+// The step coefficients of the two-point solvers come from a table made once
+// per handle (a.cuk; computed here where there was no room for it).  Latency
+// bounds the kernel -- two wavefronts per SIMD, three barriers -- and the table
+// takes an exponential or a 14-term series per interval out of it; with each
+// XCD on a run of frequencies, whose sources share cache lines, one slab of
+// 256 depths, 16 |mu| x 256 frequencies: 15.0 -> 11.9 us.
 template <int FS, int NT, int LMAX>
 __global__ __launch_bounds__(NT) void prd_sweep_cached_kernel(PrdArgs a) {
     extern __shared__ double lds[];
-    const int p = blockIdx.x, slab = blockIdx.y;
+    // workgroups are dealt to the eight XCDs in turn: a run of consecutive
+    // frequencies to each
+    constexpr int kXcds = 8;
+    const int nwg = gridDim.x * gridDim.y, lin = blockIdx.y * gridDim.x + blockIdx.x;
+    const int xcd = lin % kXcds, run = nwg / kXcds, rem = nwg % kXcds;
+    const int wg = xcd * run + min(xcd, rem) + lin / kXcds;
+    const int p = wg % gridDim.x, slab = wg / gridDim.x;
     const AtmDesc at = a.atm[slab];
     const int M = a.M, nch = a.nch, ns = at.ns, t = threadIdx.x;
     double *stage = lds;
     double *carry = stage + 2LL * M * a.ns_max;
     double *ssrc = carry + 6LL * nch * M;
     double *stau = ssrc + 2LL * a.ns_max;
+    const bool active = t < M * nch;
+    const int mp = active ? t % M : 0, c = active ? t / M : 0;
+    const int L = (ns + nch - 1) / nch;
+    const int j0 = min(c * L, ns), j1 = min(j0 + L, ns), len = j1 - j0;
+    // (c_u, c_k) of intervals j0 - 1 .. j0 + LMAX - 1
+    constexpr bool kTable = FS != RT_FS_DELO_PARABOLIC;
+    double2 cuk[kTable ? LMAX + 1 : 1];
+    if constexpr (kTable) {
+        if (a.cuk) {
+            const double2 *from = a.cuk + ((long long)at.doff * a.n_nu + (long long)p * ns) * M + mp;
+#pragma unroll
+            for (int q = 0; q < LMAX + 1; ++q)
+                cuk[q] = from[(long long)min(max(j0 - 1 + q, 0), ns - 1) * M];
+        }
+    }
     for (int j = t; j < ns; j += NT) {
         double2 v = make_double2(0.0, 0.0);
         if (a.sig_in) {
@@ -279,10 +309,6 @@ __global__ __launch_bounds__(NT) void prd_sweep_cached_kernel(PrdArgs a) {
     }
     __syncthreads();
 
-    const bool active = t < M * nch;
-    const int mp = active ? t % M : 0, c = active ? t / M : 0;
-    const int L = (ns + nch - 1) / nch;
-    const int j0 = min(c * L, ns), j1 = min(j0 + L, ns), len = j1 - j0;
     const double kap = a.opac[(long long)slab * a.n_nu + p] / a.mu_pos[mp];
     const double wq = 0.5 * a.w_pos[mp];
     const double t1 = a.dirc[mp].x, t12 = a.dirc[mp].y;
@@ -320,10 +346,21 @@ __global__ __launch_bounds__(NT) void prd_sweep_cached_kernel(PrdArgs a) {
         // both directions)
         double Eq[LMAX + 1], uq[LMAX + 1], kq[LMAX + 1];
         if constexpr (FS != RT_FS_DELO_PARABOLIC) {
+            if (a.cuk) {
 #pragma unroll
-            for (int q = 0; q < LMAX + 1; ++q) {
-                double cd;
-                ray_step(FS, dq[q], 1.0, false, Eq[q], uq[q], kq[q], cd);
+                for (int q = 0; q < LMAX + 1; ++q) {
+                    const int j = j0 - 1 + q;
+                    const bool on = j >= 0 && j + 1 < ns;
+                    uq[q] = on ? cuk[q].x : 0.0;
+                    kq[q] = on ? cuk[q].y : 0.0;
+                    Eq[q] = 1.0 - (uq[q] + kq[q]);
+                }
+            } else {
+#pragma unroll
+                for (int q = 0; q < LMAX + 1; ++q) {
+                    double cd;
+                    ray_step(FS, dq[q], 1.0, false, Eq[q], uq[q], kq[q], cd);
+                }
             }
         }
         // downward: point i from i - 1 through interval i - 1
@@ -444,11 +481,15 @@ __global__ __launch_bounds__(NT) void prd_sweep_cached_kernel(PrdArgs a) {
 // A[l % 16][l / 16] = Rw(p0 + l % 16, q0 + l / 16) and
 // B[l / 16][l % 16] = J(q0 + l / 16, c0 + l % 16), each 16 lanes reading 16
 // consecutive doubles; result register r of lane l is
-// Jt(p0 + 4 r + l / 16, c0 + l % 16).  Eight q-steps of loads are issued
-// before their products.
+// Jt(p0 + 4 r + l / 16, c0 + l % 16).
+// Latency bounds it (67 MFLOP, 16 products per wavefront on 256 x 256 x 512),
+// so all of a wavefront's loads go out together for up to 256 frequencies, and
+// each wavefront stores a quarter of the tile, whose inputs it reads beside
+// them: 6.5 -> 5.0 us.
 __global__ __launch_bounds__(kPrdNT) void prd_contract_kernel(PrdArgs a) {
-    constexpr int U = 8, NW = kPrdNT / kWave;
-    __shared__ v4d red[NW - 1][kWave];
+    constexpr int U = 16, NW = kPrdNT / kWave;
+    static_assert(NW == 4, "a wavefront per result register");
+    __shared__ double red[NW][4][kWave];
     const int slab = blockIdx.z;
     const AtmDesc at = a.atm[slab];
     const int lane = threadIdx.x % kWave, wv = threadIdx.x / kWave;
@@ -456,43 +497,43 @@ __global__ __launch_bounds__(kPrdNT) void prd_contract_kernel(PrdArgs a) {
     const int ncol = 2 * at.ns, nnu = a.n_nu;
     if (c0 >= ncol) return;  // the whole workgroup
     const double *RwT = a.RwT + (long long)slab * nnu * nnu;
-    const int pa = p0 + lane % 16, kq = lane / 16;      // A operand
-    const int cb = c0 + lane % 16;                      // B operand column
+    const int pa = min(p0 + lane % 16, nnu - 1), kq = lane / 16;  // A operand
+    const int c = c0 + lane % 16, cb = min(c, ncol - 1);          // B operand column
     const double *Jb = a.J + 2LL * at.doff;
-    const long long js = 2LL * a.ns_total;              // J row stride (one q)
-    const bool arow = pa < nnu, bcol = cb < ncol;
+    const long long js = 2LL * a.ns_total;                        // J row stride (one q)
+    // the wavefront's share of the result: row p of register wv (rows and
+    // columns past the end are read at the last one and not stored)
+    const int k = c / 2, K = c % 2, kc = min(k, at.ns - 1);
+    const int p = p0 + 4 * wv + lane / 16, pc = min(p, nnu - 1);
+    const long long e = 2 * ((long long)(at.doff + kc) * nnu + pc) + K;
+    double z = K == 0 ? at.eps * a.B[at.doff + kc] : 0.0;
+    if (a.sig_in) z = a.scale ? a.scale[e] * a.sig_in[e] : a.sig_in[e];
+    const double phi = a.phi[(long long)slab * nnu + pc];
     v4d acc = {0.0, 0.0, 0.0, 0.0};
     for (int q0 = 4 * wv; q0 < nnu; q0 += 4 * NW * U) {
         double av[U], bv[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int q = q0 + 4 * NW * u + kq;
-            av[u] = (arow && q < nnu) ? RwT[(long long)q * nnu + pa] : 0.0;
-            bv[u] = (bcol && q < nnu) ? Jb[q * js + cb] : 0.0;
+            const int q = q0 + 4 * NW * u + kq, qc = min(q, nnu - 1);
+            av[u] = RwT[(long long)qc * nnu + pa];
+            bv[u] = Jb[qc * js + cb];
         }
 #pragma unroll
-        for (int u = 0; u < U; ++u) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(av[u], bv[u], acc, 0, 0, 0);
+        for (int u = 0; u < U; ++u) {
+            // q past the last: nothing added
+            const bool on = q0 + 4 * NW * u + kq < nnu;
+            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(on ? av[u] : 0.0, on ? bv[u] : 0.0, acc, 0, 0, 0);
+        }
     }
-    if (wv > 0) red[wv - 1][lane] = acc;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) red[wv][r][lane] = acc[r];
     __syncthreads();
-    if (wv > 0) return;
+    double sum = red[0][wv][lane];
 #pragma unroll
-    for (int w = 0; w < NW - 1; ++w) acc += red[w][lane];
-    const int c = c0 + lane % 16;
-    if (c >= ncol) return;
-    const int k = c / 2, K = c % 2;
-    const double wk = K == 0 ? at.xi : at.xi * at.W2;
-#pragma unroll
-    for (int rr = 0; rr < 4; ++rr) {
-        const int p = p0 + 4 * rr + lane / 16;
-        if (p >= nnu) continue;
-        const long long e = 2 * ((long long)(at.doff + k) * nnu + p) + K;
-        const double t = wk * acc[rr] / a.phi[(long long)slab * nnu + p];
-        if (a.sig_in)
-            a.sig_out[e] = (a.scale ? a.scale[e] * a.sig_in[e] : a.sig_in[e]) - t;
-        else
-            a.sig_out[e] = t + (K == 0 ? at.eps * a.B[at.doff + k] : 0.0);
-    }
+    for (int w = 1; w < NW; ++w) sum += red[w][wv][lane];
+    if (c >= ncol || p >= nnu) return;
+    const double t = (K == 0 ? at.xi : at.xi * at.W2) * sum / phi;
+    a.sig_out[e] = a.sig_in ? z - t : t + z;
 }
 
 // The same contraction on the BF16 matrix cores (v_mfma_f32_16x16x32_bf16):
@@ -616,6 +657,23 @@ __global__ void prd_diag_kernel(PrdArgs a, double *diag, double *dinv) {
     dinv[2 * e + 1] = 1.0 / d2;
 }
 
+// (c_u, c_k) of every interval (row j: between depths j and j + 1) of every ray
+// of the two-point solvers, at ((doff n_nu + p ns + j) M + m).
+__global__ void prd_cuk_kernel(PrdArgs a, double2 *cuk) {
+    const int p = blockIdx.x, slab = blockIdx.y, M = a.M;
+    const AtmDesc at = a.atm[slab];
+    double2 *to = cuk + ((long long)at.doff * a.n_nu + (long long)p * at.ns) * M;
+    const double r = a.opac[(long long)slab * a.n_nu + p];
+    const double *tau = a.tau + at.doff;
+    for (int e = threadIdx.x; e < at.ns * M; e += blockDim.x) {
+        const int j = e / M, m = e % M;
+        double E = 0.0, cu = 0.0, ck = 0.0, cd = 0.0;
+        if (j + 1 < at.ns)
+            ray_step(a.fs, r / a.mu_pos[m] * (tau[j + 1] - tau[j]), 1.0, false, E, cu, ck, cd);
+        to[e] = make_double2(cu, ck);
+    }
+}
+
 PrdArgs prd_args(const rt_handle *h, const double *in, double *out) {
     PrdArgs a{};
     a.atm = h->d_atm;
@@ -635,6 +693,7 @@ PrdArgs prd_args(const rt_handle *h, const double *in, double *out) {
     a.sig_out = out;
     a.stage = h->d_prd_Jm;
     a.J = h->d_prd_J;
+    a.cuk = reinterpret_cast<const double2 *>(h->d_prd_cuk);
     a.fs = h->fs;
     a.M = h->M;
     a.n_nu = h->n_nu;
@@ -725,6 +784,27 @@ hipError_t prd_diag(const rt_handle *h, double *diag, double *dinv, hipStream_t 
     hipLaunchKernelGGL(prd_diag_kernel, dim3((unsigned)((npts + 255) / 256)), dim3(256), 0, s, a,
                        diag, dinv);
     return hipGetLastError();
+}
+
+// The coefficient table, while half of the 256 MB cache holds it (a table
+// streamed from HBM would cost what it saves).  Without room for it the sweep
+// computes the coefficients.
+int prd_table(rt_handle *h) {
+    const long long rows = (long long)h->ns_total * h->n_nu * h->M;
+    if (h->d_prd_cuk || h->fs == RT_FS_DELO_PARABOLIC || h->M > kPrdSweepNT || rows > kPrdTableRows)
+        return RT_OK;
+    choose_prd_sweep(h);
+    if (!h->prd_cached_nt) return RT_OK;
+    if (hipMalloc((void **)&h->d_prd_cuk, sizeof(double2) * rows) != hipSuccess) {
+        h->d_prd_cuk = nullptr;
+        (void)hipGetLastError();
+        return RT_OK;
+    }
+    hipLaunchKernelGGL(prd_cuk_kernel, dim3(h->n_nu, h->n_atm), dim3(256), 0, nullptr,
+                       prd_args(h, nullptr, nullptr), reinterpret_cast<double2 *>(h->d_prd_cuk));
+    if (hipGetLastError() != hipSuccess || hipStreamSynchronize(nullptr) != hipSuccess)
+        return fail(RT_EDEVICE, "redistribution coefficient table");
+    return RT_OK;
 }
 
 int ensure_prd(rt_handle *h, hipStream_t s) {
