@@ -28,7 +28,8 @@ OBJDIR = os.path.join(PKG, "_build")
 # the sources of the sweep's kernels and launchers: their hash is built into
 # the library, and stored launch plans and counter readings are trusted only
 # while it is unchanged
-SWEEP_SOURCES = ["rt_sweep_kernel.h", "rt_sweep.hip", "rt_sweep_f32.hip", "rt_sweep_f64.hip",
+SWEEP_SOURCES = ["rt_sweep_kernel.h", "rt_finalize.h", "rt_sweep.hip", "rt_sweep_f32.hip",
+                 "rt_sweep_f64.hip",
                  "rt_sweep_f32_w.hip", "rt_sweep_f64_w.hip", "rt_sweep_f32_rc.hip",
                  "rt_sweep_f64_rc.hip", "rt_sweep_f64_par.hip", "rt_coef.h"]
 

@@ -415,6 +415,7 @@ static SweepArgs sweep_args(rt_handle *h, const double *in, const double *scale,
     a.dtau = h->d_dtau;
     a.fs = h->fs;
     a.M = h->M;
+    a.spread = h->plan_tail ? 0 : h->spread;
     a.dirc = h->d_dirc;
     a.Qs = h->d_Qs;
     a.sig_in = in;
@@ -446,22 +447,24 @@ hipError_t apply_operator_into(rt_handle *h, const double *in, double *out, doub
     int W;
     bool pf;
     sweep_config(h, false, &W, &pf);
+    a.whole = h->whole_slabs ? 1 : 0;
     hipError_t e = launch_sweep(h->L, W, pf, false, coef_mode_of(h, false), a, plan_blocks(h),
                                 h->ns_max, s);
-    if (e != hipSuccess) return e;
+    if (e != hipSuccess || a.whole) return e;
     return launch_finalize(a, h->n_atm, h->ns_max, plan_nblk_max(h), s);
 }
 
 hipError_t apply_operator(rt_handle *h, const double *in, const double *scale, double *out,
                           const int *mask, bool fp32, int mode, hipStream_t s) {
     fp32 = sweeps_fp32(h, fp32);
-    const SweepArgs a = sweep_args(h, in, scale, out, mask, fp32, mode);
+    SweepArgs a = sweep_args(h, in, scale, out, mask, fp32, mode);
+    a.whole = h->whole_slabs && !h->plan_tail ? 1 : 0;
     int W;
     bool pf;
     sweep_config(h, fp32, &W, &pf);
     hipError_t e = launch_sweep(h->L, W, pf, fp32, coef_mode_of(h, fp32), a, plan_blocks(h),
                                 h->ns_max, s);
-    if (e != hipSuccess) return e;
+    if (e != hipSuccess || a.whole) return e;
     return launch_finalize(a, h->n_atm, h->ns_max, plan_nblk_max(h), s);
 }
 
@@ -662,7 +665,11 @@ int rt_setup(rt_handle **out, const rt_problem *p, const rt_options *o) {
     std::vector<AtmDesc> atm_t(h->n_atm);
     std::vector<BlockDesc> blk_t_h;
     // Waves per block, waves per direction and wave-batches per wave.
-    h->W = opt.sweep_waves ? opt.sweep_waves : sweep_waves(h->L, false);
+    //
+    // Four waves per block; eight for a single slab, whose Arnoldi step adds up
+    // the blocks' sums in one workgroup (200 points, 20 x 101 rays: GMRES 1.55
+    // -> 1.51 ms, the operator alone the same).
+    h->W = opt.sweep_waves ? opt.sweep_waves : h->n_atm == 1 && h->L <= 8 ? 8 : 4;
     const long long dirs_total = (long long)h->n_atm * h->M;
     long long batches_total = 0;
     for (int n : h->ns) batches_total += (long long)h->M * slab_tiles(n, h->L, h->nc).nwb;
@@ -677,6 +684,20 @@ int rt_setup(rt_handle **out, const rt_problem *p, const rt_options *o) {
     int wpd = h->W;
     if (opt.wave_batches == 0)
         while (wpd > 1 && dirs_total * (wpd / 2) >= 5 * 4 * 256) wpd /= 2;
+    // One small slab: all of its directions in one block if that leaves a wave
+    // at most four batches; the block then ends the operator itself and the
+    // finalize launch goes (40 points, 8 x 21 rays: 9.8 -> 7.2 us back to back).
+    {
+        int w1 = h->W;
+        while (w1 > 1 && (h->W / w1) < h->M) w1 /= 2;
+        const int nwb = slab_tiles(h->ns[0], h->L, h->nc).nwb;
+        if (opt.wave_batches == 0 && h->n_atm == 1 && h->L == 4 && h->W / w1 >= h->M &&
+            (nwb + w1 - 1) / w1 <= 4 &&
+            (size_t)(h->W + 1) * 2 * h->ns_max * sizeof(double) <= (size_t)kSweepLdsBudget) {
+            wpd = w1;
+            h->whole_slabs = true;
+        }
+    }
     // Small ones: several blocks per direction, two waves per SIMD in all but
     // at least two batches per wave (below that a block's fixed part costs
     // more than the shorter chain saves).  With about 48 blocks in all
@@ -699,7 +720,7 @@ int rt_setup(rt_handle **out, const rt_problem *p, const rt_options *o) {
         d.bstride = t.bstride;
         d.ray_off = a * rays;
         int nb = std::min(std::min(nb_fill, 32), (d.nwb + wpd - 1) / wpd);
-        if (wpd < h->W) nb = (d.nwb + wpd - 1) / wpd;
+        if (wpd < h->W || h->whole_slabs) nb = (d.nwb + wpd - 1) / wpd;
         if (opt.wave_batches > 0) nb = opt.wave_batches;
         const int dpb = h->W / wpd;  // directions per block
         const int dgroups = (h->M + dpb - 1) / dpb;
@@ -803,6 +824,12 @@ int rt_setup(rt_handle **out, const rt_problem *p, const rt_options *o) {
         }
     };
     order_blocks(h->blk_h);
+    // A single slab of few blocks: all of them on one XCD (workgroups go to
+    // the 8 in turn: every eighth place of the grid, the others empty), so that
+    // the workgroup that reads their sums, the first of its grid, finds them in
+    // its L2: 200 points, 20 x 101 rays, 40 blocks of 8 waves: GMRES 1.51 ->
+    // 1.42 ms; the operator alone 9.8 us either way.
+    if (h->n_atm == 1 && h->n_blocks > 1 && h->n_blocks <= 64 && h->ns_max <= 512) h->spread = 3;
     // the tail plan only where it differs
     const bool tail_plan = blk_t != blk;
     if (tail_plan) {

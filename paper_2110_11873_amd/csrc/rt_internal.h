@@ -105,6 +105,8 @@ struct SweepArgs {
     int src_lds;             // byte offset of the sources in the sweep's LDS (set at launch)
     int fs;                  // formal solver (coefficients computed in the sweep)
     int M;                   // directions |mu|
+    int spread;              // log2 of the grid places per block
+    int whole;               // 1: every slab is one block, which applies the last step itself
     int part_f32;            // 1: the partial sums are FP32 (written by an FP32 sweep)
 };
 
@@ -144,9 +146,6 @@ constexpr int kTailWb = 8;
 // padding).
 constexpr int chunk_len_step(int L) { return L >= 16 ? L / 8 : 1; }
 constexpr int chunk_len_min(int L) { return L / 2 + chunk_len_step(L); }
-
-// Waves per sweep block for a chunk length and precision (automatic choice).
-int sweep_waves(int L, bool fp32);
 
 // Launch helpers (rt_sweep.hip).  launch_sweep writes the per-block partial
 // quadrature sums; launch_finalize turns them into sigma_out.
@@ -249,6 +248,8 @@ struct rt_handle {
     int W = 4;                 // waves per sweep block the plan was made for
     int NB = 1;                // wave-batches per wave (per block: W * NB)
     int n_blocks = 0;
+    int spread = 0;            // log2 of the grid places per block (see rt_setup)
+    bool whole_slabs = false;  // every slab is one block: no finalize pass
     int nblk_max = 0, nblk_max_tail = 0;  // most blocks of one slab, per plan
     long long n_pairs = 0, n_partial = 0;
     long long n_partial_main = 0;  // partial sums of the main plan's blocks

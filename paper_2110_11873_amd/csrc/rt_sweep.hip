@@ -15,13 +15,14 @@
 //    (the mu > 0 ray) with the step I_k = E I_u + c_u S_u + c_k S_k,
 //    E = 1 - c_u - c_k (true of both DELO-linear and the trapezoidal rule,
 //    which reproduce a constant source exactly).  The C chunks of a ray sit in
-//    C adjacent lanes; a chunk is swept once with zero inflow, the affine
-//    maps I_out = P I_in + e of the chunks are composed by a lane scan
-//    (row-local DPP shifts, then row broadcasts), and the inflow's share T_k I_in (T_k
-//    the transmission from the chunk's entry to point k, kept from the sweep)
-//    is added at every point.  The step coefficients are read once per
-//    launch, in a tile order where a wavefront's 64 lanes read 64 consecutive
-//    pairs, one ray batch ahead of use.
+//    C adjacent lanes; a first pass over a chunk with zero inflow gives its
+//    affine map I_out = P I_in + e, the maps are composed by a lane scan
+//    (row-local DPP shifts, then row broadcasts), and a second pass starts
+//    from the inflow that the scan gives: one recurrence more, but no
+//    transmission kept and no share of the inflow added at each point.  The
+//    step coefficients are read once per launch, in a tile order where a
+//    wavefront's 64 lanes read 64 consecutive pairs, and stay in registers
+//    over both passes.
 //  * J step (eqs. J00/J02, S00/S02).  Each lane accumulates
 //    q (I_down + I_up) and the T-weighted combination for J20 over all the
 //    rays it handles, in registers; the rays of a wave are summed by an xor
@@ -35,6 +36,7 @@
 #include <type_traits>
 
 #include "rt_coef.h"
+#include "rt_finalize.h"
 #include "rt_internal.h"
 
 namespace rt {
@@ -246,36 +248,6 @@ int chunk_len(int ns, int C, int L) {
 //   mode 1: sigma_out = xi [J00, W2 J20] + [eps B, 0].
 // One thread per depth point.
 // --------------------------------------------------------------------------
-// One workgroup per (256 depth points, slab): the slab's descriptor is a
-// uniform load, so the partial sums are one memory round trip from the start.
-// sigma_out at point k of slab atm from its quadrature sums over the
-// sweep's blocks (J0, J2): the source part of the quadrature and the
-// scattering step (operator), or the right-hand side.
-__device__ inline void finalize_point(const SweepArgs &a, int atm, const AtmDesc &at, int k,
-                                      double J0, double J2) {
-    const int kk = at.doff + k;
-    const long long e = 2LL * kk;
-    double o0, o2;
-    if (a.mode == 0) {
-        double z0 = a.sig_in[e], z2 = a.sig_in[e + 1];
-        if (a.scale) {
-            z0 *= a.scale[e];
-            z2 *= a.scale[e + 1];
-        }
-        // source part of the quadrature: sum over all rays of q S
-        const double4 Q = a.Qs[atm];
-        J0 += z0 * Q.x + z2 * Q.y;
-        J2 += z0 * Q.y + z2 * Q.z;
-        o0 = z0 - at.xi * J0;
-        o2 = z2 - at.xi * at.W2 * J2;
-    } else {
-        o0 = at.xi * J0 + at.eps * a.B[kk];
-        o2 = at.xi * at.W2 * J2;
-    }
-    a.sig_out[e] = o0;
-    a.sig_out[e + 1] = o2;
-}
-
 // Adds the sums of blocks j0, j0 + step, ... (< nblk) at one point, eight
 // loads in flight; pJ points at the point's (J0, J2) in block 0's row.
 template <typename P>
@@ -299,6 +271,8 @@ __device__ inline void add_block_sums(const P *pJ, long long stride, int j0, int
     }
 }
 
+// One workgroup per (256 depth points, slab): the slab's descriptor is a
+// uniform load, so the partial sums are one memory round trip from the start.
 __global__ void finalize_kernel(SweepArgs a) {
     const int atm = blockIdx.y;
     if (a.mask && a.mask[atm] == 0) return;
@@ -355,16 +329,9 @@ __global__ __launch_bounds__(kFinNT) void finalize_split_kernel(SweepArgs a, int
 // --------------------------------------------------------------------------
 // launchers
 // --------------------------------------------------------------------------
-int sweep_waves(int L, bool fp32) {
-    // measured on gfx950 (512-slab batch, single slabs of 200 and 1024
-    // points): blocks of 4 waves; 8 waves only pay on single small slabs
-    (void)L;
-    (void)fp32;
-    return 4;
-}
-
 void sweep_config(const rt_handle *h, bool fp32, int *W, bool *pf) {
-    *W = h->opt.sweep_waves ? h->opt.sweep_waves : sweep_waves(h->L, fp32);
+    (void)fp32;
+    *W = h->W;
     // options.prefetch: 0 = automatic, 1 = loads on use, 2 or 3 = one batch
     // ahead (compiled for chunks up to 8); automatic: on use, which measured
     // as fast or faster at four waves per SIMD

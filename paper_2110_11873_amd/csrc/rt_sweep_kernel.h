@@ -17,13 +17,15 @@
 // of the interval, kappa = r_p / |mu| per ray, dtau per interval.  Each
 // block writes the 2 ns quadrature sums of its rays to its own slot of
 // `partial`; the finalize pass adds the slots of a slab in block order and
-// applies sigma_out = z - xi [J00, W2 J20].
+// applies sigma_out = z - xi [J00, W2 J20] (a block that holds all rays of its
+// slab applies it itself).
 #pragma once
 
 #include <hip/hip_runtime.h>
 
 #include <type_traits>
 
+#include "rt_finalize.h"
 #include "rt_internal.h"
 
 namespace rt {
@@ -637,6 +639,19 @@ __device__ __forceinline__ void sweep_rays(const SweepArgs &a, const BlockDesc &
             }
         }
         __syncthreads();
+        if constexpr (LE <= 4) {  // plans of chunk length 4 only: longer bodies keep their registers
+            if (a.whole) {  // this block has all of the slab's rays
+                for (int k = threadIdx.x; k < ns; k += nthr) {
+                    T s0 = sacc[2 * k], s2 = sacc[2 * k + 1];
+                    for (int w = 1; w < W; ++w) {
+                        s0 += sacc[(long long)w * 2 * ns + 2 * k];
+                        s2 += sacc[(long long)w * 2 * ns + 2 * k + 1];
+                    }
+                    finalize_point(a, bd.atm, at, k, (double)s0, (double)s2);
+                }
+                return;
+            }
+        }
         for (int e = threadIdx.x; e < 2 * ns; e += nthr) {
             T s = sacc[e];
             for (int w = 1; w < W; ++w) s += sacc[(long long)w * 2 * ns + e];
@@ -711,7 +726,8 @@ template <typename T, int L, int W, int PF, int CM>
 __global__ __launch_bounds__(kWave *W)
 __attribute__((amdgpu_waves_per_eu(MinWaves<T, L, CM>::value, 8))) void sweep_kernel(SweepArgs a) {
     extern __shared__ unsigned char smem_raw[];
-    const BlockDesc bd = a.blk[blockIdx.x];
+    if (blockIdx.x & ((1u << a.spread) - 1)) return;  // left empty: one slab on one XCD
+    const BlockDesc bd = a.blk[blockIdx.x >> a.spread];
     if (a.mask && a.mask[bd.atm] == 0) return;  // uniform over the block
     const AtmDesc at = a.atm[bd.atm];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
@@ -749,12 +765,12 @@ hipError_t launch_tw(SweepArgs a, bool pf, int nblocks, int ns_max, hipStream_t 
     const size_t lds = a.src_lds + row;
     if constexpr (L <= 8 && CM == kCoefPairs) {
         if (pf) {
-            hipLaunchKernelGGL((sweep_kernel<T, L, W, 1, CM>), dim3(nblocks), dim3(kWave * W), lds,
+            hipLaunchKernelGGL((sweep_kernel<T, L, W, 1, CM>), dim3(nblocks << a.spread), dim3(kWave * W), lds,
                                s, a);
             return hipGetLastError();
         }
     }
-    hipLaunchKernelGGL((sweep_kernel<T, L, W, 0, CM>), dim3(nblocks), dim3(kWave * W), lds, s, a);
+    hipLaunchKernelGGL((sweep_kernel<T, L, W, 0, CM>), dim3(nblocks << a.spread), dim3(kWave * W), lds, s, a);
     return hipGetLastError();
 }
 

@@ -64,3 +64,39 @@ def test_block_plans(plan, fs):
         r = b - O.apply(p, host(x))
         for s in O._slices(p):
             assert np.linalg.norm(r[s]) < 1e-9 * np.linalg.norm(b[s])
+
+
+# depths, directions, frequencies of one slab; whether one block holds it
+SINGLE = [(40, 4, 21, True), (2, 1, 2, True), (33, 8, 13, True), (256, 8, 3, True), (17, 5, 9, True),
+          (65, 2, 31, True), (40, 9, 21, False), (200, 10, 101, False)]
+
+
+@pytest.mark.parametrize("shape", SINGLE, ids=lambda s: "x".join(map(str, s[:3])))
+@pytest.mark.parametrize("fs", ["delo_linear", "implicit_euler", "delo_parabolic"])
+def test_one_slab(shape, fs):
+    """One slab: in one block, which ends the operator itself, or in several
+    blocks on one XCD; the same result in place and with the partial sums in
+    the library's array."""
+    ns, m, n_nu, whole = shape
+    p = W.make_slabs([ns], [(1e-3, 1e4)], 2 * m, n_nu, 4.0, [1e-3], [1e-2], [0.5],
+                     formal_solver=fs)
+    v = W.random_vector(p.n_unknowns, ns)
+    ref = O.apply(p, v)
+    scale = np.abs(v).max() + np.abs(v - ref).max()
+    with B.setup(p, rtol=1e-10, maxit=20000) as h:
+        assert (h.plan_info()["blocks"] == 1) == whole
+        y = h.apply_op(dev(v))
+        assert np.abs(host(y) - ref).max() <= 1e-12 * scale
+        x = dev(v)
+        assert torch.equal(h.apply_op(x, x), y)
+        if fs != "delo_parabolic":
+            assert torch.equal(h.apply_op_noalloc(dev(v)), y)
+        assert np.abs(host(h.apply_op_fp32(dev(v))) - ref).max() < 1e-5 * scale
+        b = O.rhs(p)
+        assert np.abs(host(h.get_rhs()) - b).max() <= 1e-12 * np.abs(b).max()
+        for solve in (h.solve_gmres, h.solve_bicgstab):
+            x = dev(W.initial_guess(p))
+            rc, _ = solve(x)
+            assert rc == 0
+            r = b - O.apply(p, host(x))
+            assert np.linalg.norm(r) < 2e-10 * np.linalg.norm(b)
