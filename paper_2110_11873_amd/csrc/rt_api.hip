@@ -415,7 +415,6 @@ static SweepArgs sweep_args(rt_handle *h, const double *in, const double *scale,
     a.dtau = h->d_dtau;
     a.fs = h->fs;
     a.M = h->M;
-    a.spread = h->plan_tail ? 0 : h->spread;
     a.dirc = h->d_dirc;
     a.Qs = h->d_Qs;
     a.sig_in = in;
@@ -432,7 +431,8 @@ static SweepArgs sweep_args(rt_handle *h, const double *in, const double *scale,
 hipError_t apply_sweep(rt_handle *h, const double *in, const double *scale, const int *mask,
                        bool fp32, hipStream_t s) {
     fp32 = sweeps_fp32(h, fp32);
-    const SweepArgs a = sweep_args(h, in, scale, nullptr, mask, fp32, 0);
+    SweepArgs a = sweep_args(h, in, scale, nullptr, mask, fp32, 0);
+    a.spread = h->plan_tail ? 0 : h->spread;
     int W;
     bool pf;
     sweep_config(h, fp32, &W, &pf);
@@ -828,7 +828,7 @@ int rt_setup(rt_handle **out, const rt_problem *p, const rt_options *o) {
     // the 8 in turn: every eighth place of the grid, the others empty), so that
     // the workgroup that reads their sums, the first of its grid, finds them in
     // its L2: 200 points, 20 x 101 rays, 40 blocks of 8 waves: GMRES 1.51 ->
-    // 1.42 ms; the operator alone 9.8 us either way.
+    // 1.42 ms.  The operator alone ends in a pass over all XCDs and keeps them.
     if (h->n_atm == 1 && h->n_blocks > 1 && h->n_blocks <= 64 && h->ns_max <= 512) h->spread = 3;
     // the tail plan only where it differs
     const bool tail_plan = blk_t != blk;
