@@ -555,20 +555,15 @@ int rt_num_unknowns(const rt_handle *h) { return h ? h->n_unk : 0; }
 
 void rt_destroy(rt_handle *h) {
     if (!h) return;
-    void *ptrs[] = {h->d_tau,   h->d_B,     h->d_opac,    h->d_phi,     h->d_mu_pos, h->d_w_pos,
-                    h->d_w_nu,  h->d_wphi,  h->d_pt_atm, h->d_atm,    h->d_blk,     h->d_rayc,   h->d_coef64,
-                    h->d_atm_tail, h->d_blk_tail,
-                    h->d_rayc_nu, h->d_opac_c, h->d_wphi_c, h->d_qt,      h->d_dirc,    h->d_Qs,
-                    h->d_coef32, h->d_partial, h->d_diag,  h->d_dinv,   h->d_b,
-                    h->d_V,     h->d_H,     h->d_cs,      h->d_sn,      h->d_g,      h->d_w,
-                    h->d_r,     h->d_rh,    h->d_p,       h->d_v,       h->d_s,      h->d_t,
-                    h->d_cq,    h->d_state, h->d_active,  h->d_cycle,   h->d_count,
-                    h->d_ew,    h->d_asm_dg, h->d_asm_sc, h->d_asm_task, h->d_asm_xt,
-                    h->d_asm_tt, h->d_asm_tile0, h->d_A,
-                    h->d_pz,    h->d_ones,  h->d_LU,      h->d_piv,     h->d_sing,
-                    h->d_mu_idx, h->d_fsig, h->d_Rw,   h->d_Rw_bf, h->d_prd_Jm,
-                    h->d_prd_J, h->d_prd_cuk, h->d_prd_diag, h->d_prd_dinv, h->d_w64, h->d_w32, h->d_kt,
-                    h->d_dtau, h->seg_ws[0], h->seg_ws[1], h->d_lu_order, h->d_perm, h->d_tri_order};
+    void *ptrs[] = {h->d_tau, h->d_rayc, h->d_coef64, h->d_rayc_nu, h->d_qt, h->d_dirc, h->d_Qs,
+                    h->d_coef32, h->d_partial, h->d_diag, h->d_dinv, h->d_b, h->d_V, h->d_H,
+                    h->d_cs, h->d_sn, h->d_g, h->d_w, h->d_r, h->d_rh, h->d_p, h->d_v, h->d_s,
+                    h->d_t, h->d_cq, h->d_state, h->d_active, h->d_cycle, h->d_count, h->d_ew,
+                    h->d_asm_dg, h->d_asm_sc, h->d_asm_task, h->d_asm_xt, h->d_asm_tt,
+                    h->d_asm_tile0, h->d_A, h->d_pz, h->d_ones, h->d_LU, h->d_piv, h->d_sing,
+                    h->d_fsig, h->d_Rw, h->d_Rw_bf, h->d_prd_Jm, h->d_prd_J, h->d_prd_cuk,
+                    h->d_prd_diag, h->d_prd_dinv, h->d_w64, h->d_w32, h->d_kt, h->seg_ws[0],
+                    h->seg_ws[1], h->d_lu_order, h->d_perm};
     clear_graphs(h);
     if (h->gstream) (void)hipStreamDestroy(h->gstream);
     for (hipEvent_t e : h->gev)
@@ -860,84 +855,90 @@ int rt_setup(rt_handle **out, const rt_problem *p, const rt_options *o) {
             return _rc;      \
         }                    \
     } while (0)
-    RT_TRY(dalloc(&h->d_tau, acc));
-    RT_TRY(dalloc(&h->d_B, acc));
-    RT_TRY(dalloc(&h->d_opac, nphi));
-    RT_TRY(dalloc(&h->d_phi, nphi));
-    RT_TRY(dalloc(&h->d_mu_pos, h->M));
-    RT_TRY(dalloc(&h->d_mu_idx, (size_t)2 * h->n_mu));
+    // the coefficient tiles the handle's sweeps stream, (kappa, 1 / kappa) per
+    // ray and the depth steps for those that derive coefficients
+    const int cm64 = coef_mode_of(h, false), cm32 = coef_mode_of(h, true);
+    const bool derive = cm64 != kCoefPairs || cm32 != kCoefPairs;
+    std::vector<double> dtau(derive ? acc : 0, 0.0);
+    if (derive)
+        for (int a = 0; a < h->n_atm; ++a)
+            for (int k = 0; k + 1 < h->ns[a]; ++k)
+                dtau[h->doff[a] + k] = p->tau[h->doff[a] + k + 1] - p->tau[h->doff[a] + k];
+    mu_index.resize(2 * (size_t)h->n_mu);  // and back: the |mu| of each index of the caller's
+    for (int m = 0; m < h->M; ++m)
+        mu_index[h->n_mu + mu_index[2 * m]] = mu_index[h->n_mu + mu_index[2 * m + 1]] = m;
+    // the triangular solves take a workgroup per slab, two of them per CU at
+    // a time: largest first, every other run of 256 (one per CU) reversed, so
+    // that a CU's slabs add up to similar sizes
+    std::vector<int> order(h->n_atm);
+    std::iota(order.begin(), order.end(), 0);
+    std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return h->ns[x] > h->ns[y]; });
+    for (size_t i = 256; i < order.size(); i += 512)
+        std::reverse(order.begin() + i, order.begin() + std::min(i + 256, order.size()));
+
+    // what the host made or was given: one allocation, which d_tau, its first
+    // part, stands for; small parts go in one copy, as each call costs more
+    // than its bytes (set-up of a 40-point slab 310 -> 79 us; parts of MB are
+    // faster without the staging, 512 slabs 3.2 -> 3.0 ms)
+    {
+        constexpr size_t kStage = 256 << 10, kPart = 256;
+        struct Part {
+            void **dst;
+            const void *src;
+            size_t bytes, off;
+        };
+        std::vector<Part> parts;
+        size_t total = 0;
+        const auto put = [&](auto **dst, const auto *src, size_t n) {
+            parts.push_back({(void **)dst, src, n * sizeof(*src), total});
+            total += (n * sizeof(*src) + kPart - 1) / kPart * kPart;
+        };
+        put(&h->d_tau, p->tau, acc);
+        put(&h->d_B, B.data(), acc);
+        put(&h->d_opac, p->opac, nphi);
+        put(&h->d_phi, p->phi, nphi);
+        put(&h->d_mu_pos, mu_pos.data(), h->M);
+        put(&h->d_mu_idx, mu_index.data(), mu_index.size());
+        put(&h->d_w_pos, w_pos.data(), h->M);
+        put(&h->d_w_nu, p->w_nu, h->n_nu);
+        put(&h->d_wphi, wphi.data(), nphi);
+        put(&h->d_opac_c, opac_c.data(), nmerged);
+        put(&h->d_wphi_c, wphi_c.data(), nmerged);
+        put(&h->d_pt_atm, pt_atm.data(), acc);
+        put(&h->d_atm, h->atm_h.data(), h->n_atm);
+        put(&h->d_blk, h->blk_h.data(), h->n_blocks);
+        put(&h->d_tri_order, order.data(), h->n_atm);
+        if (derive) put(&h->d_dtau, dtau.data(), acc);
+        if (tail_plan) {
+            put(&h->d_atm_tail, atm_t.data(), h->n_atm);
+            put(&h->d_blk_tail, blk_t_h.data(), h->n_blocks_tail);
+        }
+        char *base;
+        RT_TRY(dalloc(&base, total));
+        for (const Part &q : parts) *q.dst = base + q.off;
+        if (total <= kStage) {
+            std::vector<char> stage(total);
+            for (const Part &q : parts) std::memcpy(stage.data() + q.off, q.src, q.bytes);
+            RT_TRY(h2d(base, stage.data(), total));
+        } else {
+            for (const Part &q : parts) RT_TRY(h2d(base + q.off, (const char *)q.src, q.bytes));
+        }
+    }
     RT_TRY(dalloc(&h->d_fsig, (size_t)2 * acc));
-    RT_TRY(dalloc(&h->d_w_pos, h->M));
-    RT_TRY(dalloc(&h->d_w_nu, h->n_nu));
-    RT_TRY(dalloc(&h->d_wphi, nphi));
-    RT_TRY(dalloc(&h->d_opac_c, nmerged));
-    RT_TRY(dalloc(&h->d_wphi_c, nmerged));
-    RT_TRY(dalloc(&h->d_pt_atm, acc));
-    RT_TRY(dalloc(&h->d_atm, h->n_atm));
-    RT_TRY(dalloc(&h->d_blk, h->n_blocks));
     RT_TRY(dalloc(&h->d_rayc, (size_t)h->n_atm * rays));
     RT_TRY(dalloc(&h->d_rayc_nu, nphi * h->M));
     RT_TRY(dalloc(&h->d_qt, (size_t)h->n_qt));
     RT_TRY(dalloc(&h->d_dirc, (size_t)h->M));
     RT_TRY(dalloc(&h->d_Qs, (size_t)h->n_atm));
-    // the coefficient tiles the handle's sweeps stream, (kappa, 1 / kappa) per
-    // ray and the depth steps for those that derive coefficients
-    const int cm64 = coef_mode_of(h, false), cm32 = coef_mode_of(h, true);
     if (cm64 == kCoefPairs || cm64 == kCoefParabolic) RT_TRY(dalloc(&h->d_coef64, h->n_pairs));
     if (cm32 == kCoefPairs) RT_TRY(dalloc(&h->d_coef32, h->n_pairs));
     if (cm64 == kCoefW) RT_TRY(dalloc(&h->d_w64, h->n_pairs));
     if (cm32 == kCoefW) RT_TRY(dalloc(&h->d_w32, h->n_pairs));
-    const bool derive = cm64 != kCoefPairs || cm32 != kCoefPairs;
-    if (derive) {
-        RT_TRY(dalloc(&h->d_kt, (size_t)h->n_qt));
-        RT_TRY(dalloc(&h->d_dtau, acc));
-        std::vector<double> dtau(acc, 0.0);
-        for (int a = 0; a < h->n_atm; ++a)
-            for (int k = 0; k + 1 < h->ns[a]; ++k)
-                dtau[h->doff[a] + k] = p->tau[h->doff[a] + k + 1] - p->tau[h->doff[a] + k];
-        RT_TRY(h2d(h->d_dtau, dtau.data(), acc));
-    }
+    if (derive) RT_TRY(dalloc(&h->d_kt, (size_t)h->n_qt));
     RT_TRY(dalloc(&h->d_partial, std::max<long long>(h->n_partial, 1)));
     RT_TRY(dalloc(&h->d_diag, h->n_unk));
     RT_TRY(dalloc(&h->d_dinv, h->n_unk));
     RT_TRY(dalloc(&h->d_b, h->n_unk));
-    RT_TRY(h2d(h->d_tau, p->tau, acc));
-    RT_TRY(h2d(h->d_B, B.data(), acc));
-    RT_TRY(h2d(h->d_opac, p->opac, nphi));
-    RT_TRY(h2d(h->d_phi, p->phi, nphi));
-    RT_TRY(h2d(h->d_mu_pos, mu_pos.data(), h->M));
-    mu_index.resize(2 * (size_t)h->n_mu);  // and back: the |mu| of each index of the caller's
-    for (int m = 0; m < h->M; ++m)
-        mu_index[h->n_mu + mu_index[2 * m]] = mu_index[h->n_mu + mu_index[2 * m + 1]] = m;
-    RT_TRY(h2d(h->d_mu_idx, mu_index.data(), (size_t)2 * h->n_mu));
-    RT_TRY(h2d(h->d_w_pos, w_pos.data(), h->M));
-    RT_TRY(h2d(h->d_w_nu, p->w_nu, h->n_nu));
-    RT_TRY(h2d(h->d_wphi, wphi.data(), nphi));
-    RT_TRY(h2d(h->d_opac_c, opac_c.data(), nmerged));
-    RT_TRY(h2d(h->d_wphi_c, wphi_c.data(), nmerged));
-    RT_TRY(h2d(h->d_pt_atm, pt_atm.data(), acc));
-    RT_TRY(h2d(h->d_atm, h->atm_h.data(), h->n_atm));
-    RT_TRY(h2d(h->d_blk, h->blk_h.data(), h->n_blocks));
-    if (tail_plan) {
-        RT_TRY(dalloc(&h->d_atm_tail, h->n_atm));
-        RT_TRY(dalloc(&h->d_blk_tail, h->n_blocks_tail));
-        RT_TRY(h2d(h->d_atm_tail, atm_t.data(), h->n_atm));
-        RT_TRY(h2d(h->d_blk_tail, blk_t_h.data(), h->n_blocks_tail));
-    }
-
-    // the triangular solves take a workgroup per slab, two of them per CU at
-    // a time: largest first, every other run of 256 (one per CU) reversed, so
-    // that a CU's slabs add up to similar sizes
-    {
-        std::vector<int> order(h->n_atm);
-        std::iota(order.begin(), order.end(), 0);
-        std::stable_sort(order.begin(), order.end(),
-                         [&](int x, int y) { return h->ns[x] > h->ns[y]; });
-        for (size_t i = 256; i < order.size(); i += 512)
-            std::reverse(order.begin() + i, order.begin() + std::min(i + 256, order.size()));
-        RT_TRY(dalloc(&h->d_tri_order, h->n_atm));
-        RT_TRY(h2d(h->d_tri_order, order.data(), h->n_atm));
-    }
 
     // ---- precompute: ray constants, tile coefficients, D and D^-1, b
     hipStream_t s = nullptr;
