@@ -57,7 +57,8 @@ int rt_solve_cgs(rt_handle *h, const double *b, double *x, rt_solve_info *info, 
 
 /*
  * Describe the sweep plan: chunk length L, number of sweep workgroups, number
- * of stored coefficient pairs (tiles, including padding) and of ray-interval
+ * of stored coefficient pairs (tiles, including padding; frequencies of equal
+ * opacity share theirs) and of ray-interval
  * pairs sum_slabs (ns - 1) (n_mu / 2) n_nu.  Any output pointer may be NULL.
  * Host only.
  */
