@@ -186,7 +186,7 @@ typedef struct rt_problem {
  *  check_every iterations between convergence checks read back by the host
  *              for BiCGSTAB and Richardson (16); GMRES checks once per cycle
  *  sweep_waves wavefronts per sweep workgroup: 0 = automatic, 4 or 8 (8 is
- *              available for chunk lengths up to 8)
+ *              available for chunk lengths up to 8; longer ones run with 4)
  *  graphs      1 = the kernels of one GMRES cycle (of check_every BiCGSTAB or
  *              Richardson iterations) are captured once in a HIP graph and
  *              replayed, the host testing convergence between replays;

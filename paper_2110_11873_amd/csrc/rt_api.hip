@@ -663,8 +663,11 @@ int rt_setup(rt_handle **out, const rt_problem *p, const rt_options *o) {
     //
     // Four waves per block; eight for a single slab, whose Arnoldi step adds up
     // the blocks' sums in one workgroup (200 points, 20 x 101 rays: GMRES 1.55
-    // -> 1.51 ms, the operator alone the same).
-    h->W = opt.sweep_waves ? opt.sweep_waves : h->n_atm == 1 && h->L <= 8 ? 8 : 4;
+    // -> 1.51 ms, the operator alone the same).  Eight are compiled for chunks
+    // up to 8 only: longer ones take four, also where the caller asked for eight
+    // and left the chunk to the slabs' depths.
+    h->W = opt.sweep_waves ? opt.sweep_waves : h->n_atm == 1 ? 8 : 4;
+    if (h->L > 8) h->W = 4;
     const long long dirs_total = (long long)h->n_atm * h->M;
     long long batches_total = 0;
     for (int n : h->ns) batches_total += (long long)h->M * slab_tiles(n, h->L, h->nc).nwb;
