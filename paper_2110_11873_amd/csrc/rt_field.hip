@@ -194,20 +194,27 @@ __global__ __launch_bounds__(kCachedNT) void field_sweep_cached_kernel(FieldArgs
             cu[i] = ck[i] = 0.0;
         }
     }
-    // the two directions through the chunk, from (X, Y) entering it; visit(i, X, Y) at its points
+    // the two directions through the chunk, from (X, Y) entering it; visit(i, X, Y) at its
+    // points.  What an interval outside the slab adds is left out, not multiplied by its zero
+    // coefficients: the source beside it may be no number, and the ray that enters there
+    // has only the boundary value
+    auto add = [&](int i, double su, double sk) {
+        const double v = fma(cu[i], su, ck[i] * sk);
+        return j0 + i >= 1 && j0 + i < ns ? v : 0.0;
+    };
     auto down = [&](double X, double Y, auto visit) {
 #pragma unroll
         for (int i = 0; i < LM; ++i) {
-            X = fma(E[i], X, fma(cu[i], s0[i], ck[i] * s0[i + 1]));
-            Y = fma(E[i], Y, fma(cu[i], s2[i], ck[i] * s2[i + 1]));
+            X = fma(E[i], X, add(i, s0[i], s0[i + 1]));
+            Y = fma(E[i], Y, add(i, s2[i], s2[i + 1]));
             visit(i, X, Y);
         }
     };
     auto up = [&](double X, double Y, auto visit) {
 #pragma unroll
         for (int i = LM - 1; i >= 0; --i) {
-            X = fma(E[i + 1], X, fma(cu[i + 1], s0[i + 2], ck[i + 1] * s0[i + 1]));
-            Y = fma(E[i + 1], Y, fma(cu[i + 1], s2[i + 2], ck[i + 1] * s2[i + 1]));
+            X = fma(E[i + 1], X, add(i + 1, s0[i + 2], s0[i + 1]));
+            Y = fma(E[i + 1], Y, add(i + 1, s2[i + 2], s2[i + 1]));
             visit(i, X, Y);
         }
     };
