@@ -85,7 +85,8 @@ __device__ __forceinline__ void tri_sweep(const double *A, int N, double om, dou
             val -= s0 + s1;
         }
         // rows scaled by the inverse diagonal, so a step is one broadcast and
-        // one multiply-add; columns outside the triangle count as zero
+        // one multiply-add, for the rows that the unknown enters (a row outside
+        // them would take 0 x infinity from an unknown that is no number)
         const double dc = UNIT ? 1.0 : i0 + c < N ? om / row[own + c] : 0.0;
         val *= dc;
 #pragma unroll 1
@@ -94,13 +95,13 @@ __device__ __forceinline__ void tri_sweep(const double *A, int N, double om, dou
 #pragma unroll
             for (int u = 0; u < 8; ++u) {
                 const int i = UP ? kTriB - 1 - (i8 + u) : i8 + u;
-                const double e = UNIT ? row[own + i] : row[own + i] * dc;
-                col[u] = (UP ? c < i : c > i) ? e : 0.0;
+                col[u] = UNIT ? row[own + i] : row[own + i] * dc;
             }
 #pragma unroll
             for (int u = 0; u < 8; ++u) {
                 const int i = UP ? kTriB - 1 - (i8 + u) : i8 + u;
-                val = fma(-col[u], readlane_d(val, i), val);
+                const double xi = readlane_d(val, i);
+                if (UP ? c < i : c > i) val = fma(-col[u], xi, val);
             }
         }
         if (i0 + c < N) r[i0 + c] = val;
