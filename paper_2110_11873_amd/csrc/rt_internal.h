@@ -298,7 +298,7 @@ struct rt_handle {
     int prd_nqp = 0;              // padded row length of the bf16 split (multiple of 32)
     double *d_prd_Jm = nullptr;   // per-|mu| quadrature stage (when not in LDS)
     double *d_prd_J = nullptr;    // monochromatic J, frequency-major [p][k][K]
-    double *d_prd_cuk = nullptr;  // (c_u, c_k) per interval and ray, or NULL
+    double *d_prd_cuk = nullptr;  // step coefficients per interval and ray (pack_step), or NULL
     double *d_prd_diag = nullptr, *d_prd_dinv = nullptr;
     bool prd_ready = false;
     int prd_cached_nt = 0;        // threads of the cached-coefficient sweep, 0: the general sweep

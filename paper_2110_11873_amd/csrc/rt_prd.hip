@@ -67,7 +67,7 @@ struct PrdArgs {
     double *sig_out;
     double *stage;        // global stage (when the LDS one does not fit)
     double *J;            // [n_nu][ns_total][2]
-    const double2 *cuk;   // (c_u, c_k) of every interval and ray: prd_cuk, or NULL
+    const double2 *cuk;   // step coefficients of every interval and ray (pack_step), or NULL
     int fs, M, n_nu, ns_total, ns_max, nch;
 };
 
@@ -240,6 +240,30 @@ __global__ __launch_bounds__(kPrdSweepNT) void prd_sweep_kernel(PrdArgs a) {
     }
 }
 
+// The step coefficients (E, c_u, c_k) of a two-point solver in two numbers, from
+// which unpack_step gives the three that ray_step gave, to the bit.  E = 1 - (c_u
+// + c_k) alone would be right to 1e-16 only, so that a transmission below that had
+// no correct digit.  DELO-linear: (c_u, c_k) where ray_step takes them from the
+// series and E from their sum, else (c_u, -E) with c_k = (1 - E) - c_u; the sign
+// bit tells them apart (c_k >= 0).  Trapezoidal: c_u = c_k.  Implicit Euler: c_u = 0.
+__device__ inline double2 pack_step(int fs, double d, double E, double cu, double ck) {
+    if (fs != RT_FS_DELO_LINEAR) return make_double2(E, ck);
+    return make_double2(cu, d < 0.1 ? ck : -E);
+}
+template <int FS>
+__device__ inline void unpack_step(double2 v, double &E, double &cu, double &ck) {
+    if constexpr (FS == RT_FS_DELO_LINEAR) {
+        const bool big = __double2hiint(v.y) < 0;
+        cu = v.x;
+        E = big ? -v.y : 1.0 - (cu + v.y);
+        ck = big ? (1.0 - E) - cu : v.y;
+    } else {
+        E = v.x;
+        cu = FS == RT_FS_TRAPEZOIDAL ? v.y : 0.0;
+        ck = v.y;
+    }
+}
+
 // The same sweep for one formal solver FS, each chunk held in registers.  The
 // frequency's sources and the slab's depths are staged in LDS; a lane loads
 // its chunk's points (and the one before and after it) into registers, and
@@ -256,7 +280,7 @@ __global__ __launch_bounds__(kPrdSweepNT) void prd_sweep_kernel(PrdArgs a) {
 // [2][nch][M][3], sources [ns_max][2], depths [ns_max].
 //
 // The step coefficients of the two-point solvers come from a table made once
-// per handle (a.cuk; computed here where there was no room for it).  Latency
+// per handle (a.cuk, pack_step; computed here where there was no room for it).  Latency
 // bounds the kernel -- two wavefronts per SIMD, three barriers -- and the table
 // takes an exponential or a 14-term series per interval out of it; with each
 // XCD on a run of frequencies, whose sources share cache lines, one slab of
@@ -281,7 +305,8 @@ __global__ __launch_bounds__(NT) void prd_sweep_cached_kernel(PrdArgs a) {
     const int mp = active ? t % M : 0, c = active ? t / M : 0;
     const int L = (ns + nch - 1) / nch;
     const int j0 = min(c * L, ns), j1 = min(j0 + L, ns), len = j1 - j0;
-    // (c_u, c_k) of intervals j0 - 1 .. j0 + LMAX - 1
+    // the table's rows of intervals j0 - 1 .. j0 + LMAX - 1 (the last row is the
+    // identity; no step enters the first point)
     constexpr bool kTable = FS != RT_FS_DELO_PARABOLIC;
     double2 cuk[kTable ? LMAX + 1 : 1];
     if constexpr (kTable) {
@@ -348,13 +373,7 @@ __global__ __launch_bounds__(NT) void prd_sweep_cached_kernel(PrdArgs a) {
         if constexpr (FS != RT_FS_DELO_PARABOLIC) {
             if (a.cuk) {
 #pragma unroll
-                for (int q = 0; q < LMAX + 1; ++q) {
-                    const int j = j0 - 1 + q;
-                    const bool on = j >= 0 && j + 1 < ns;
-                    uq[q] = on ? cuk[q].x : 0.0;
-                    kq[q] = on ? cuk[q].y : 0.0;
-                    Eq[q] = 1.0 - (uq[q] + kq[q]);
-                }
+                for (int q = 0; q < LMAX + 1; ++q) unpack_step<FS>(cuk[q], Eq[q], uq[q], kq[q]);
             } else {
 #pragma unroll
                 for (int q = 0; q < LMAX + 1; ++q) {
@@ -657,8 +676,8 @@ __global__ void prd_diag_kernel(PrdArgs a, double *diag, double *dinv) {
     dinv[2 * e + 1] = 1.0 / d2;
 }
 
-// (c_u, c_k) of every interval (row j: between depths j and j + 1) of every ray
-// of the two-point solvers, at ((doff n_nu + p ns + j) M + m).
+// The step coefficients (pack_step) of every interval (row j: between depths j and
+// j + 1) of every ray of the two-point solvers, at ((doff n_nu + p ns + j) M + m).
 __global__ void prd_cuk_kernel(PrdArgs a, double2 *cuk) {
     const int p = blockIdx.x, slab = blockIdx.y, M = a.M;
     const AtmDesc at = a.atm[slab];
@@ -667,10 +686,12 @@ __global__ void prd_cuk_kernel(PrdArgs a, double2 *cuk) {
     const double *tau = a.tau + at.doff;
     for (int e = threadIdx.x; e < at.ns * M; e += blockDim.x) {
         const int j = e / M, m = e % M;
-        double E = 0.0, cu = 0.0, ck = 0.0, cd = 0.0;
-        if (j + 1 < at.ns)
-            ray_step(a.fs, r / a.mu_pos[m] * (tau[j + 1] - tau[j]), 1.0, false, E, cu, ck, cd);
-        to[e] = make_double2(cu, ck);
+        double E = 1.0, cu = 0.0, ck = 0.0, cd = 0.0, d = 0.0;
+        if (j + 1 < at.ns) {
+            d = r / a.mu_pos[m] * (tau[j + 1] - tau[j]);
+            ray_step(a.fs, d, 1.0, false, E, cu, ck, cd);
+        }
+        to[e] = pack_step(a.fs, d, E, cu, ck);
     }
 }
 
