@@ -169,18 +169,30 @@ __device__ inline void parabolic_coef(double d, double dd, double &E, double &cu
 // The parabolic step's weights in the sweep's form (rt_sweep_kernel.h), for an
 // interval of optical step d and depth step h: w = w0 / d and
 // g = h^2 (2 w1 / d^2 - w0 / d) = (h / d)^2 (w2 - d w1), the second form free of
-// cancellation below d = 1 (w2 ~ d^3 / 3, d w1 ~ d^3 / 2).
-__device__ inline void parabolic_wg(double d, double h, double &w, double &g) {
+// cancellation below d = 1 (w2 ~ d^3 / 3, d w1 ~ d^3 / 2).  The step also takes E,
+// which 1 - w d gives to 1e-16 only; so the pair is (w, g) below d = 1, where E
+// is no smaller than 0.37, and (w, E) above, where g = h (2 (w - E) h / d - h w)
+// cancels by a factor of six at most.  The sign bit of the second tells them
+// apart: g <= 0 carries it (also as zero), E does not.
+__device__ inline void parabolic_pack(double d, double h, double &w, double &y) {
     if (d < 1e-100) {  // the limits; d^3 would underflow
         w = 1.0;
-        g = 0.0;
+        y = -0.0;
         return;
     }
     double E, w0, w1, w2;
     exp_moments(d, E, w0, w1, w2);
     const double r = h / d;
     w = w0 / d;
-    g = r * r * (w2 - d * w1);
+    y = d < 1.0 ? -fabs(r * r * (w2 - d * w1)) : E;
+}
+// (E, g) from the pair, 2 / kappa = 2 h / d and the steps; the identity is (1, -0)
+__device__ inline void parabolic_unpack(double w, double y, double d, double h, double rk2,
+                                        double &E, double &g) {
+    const bool thin = __double2hiint(y) < 0;
+    const double thick = h * fma(w - y, rk2, -h * w);
+    E = thin ? fma(-w, d, 1.0) : y;
+    g = thin ? y : thick;
 }
 
 __device__ inline void ray_step(int fs, double d, double dd, bool has_dn, double &E,

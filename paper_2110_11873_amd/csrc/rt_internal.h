@@ -78,8 +78,8 @@ struct RayConst {
 constexpr int kCoefPairs = 0;
 constexpr int kCoefW = 1;
 constexpr int kCoefRecompute = 2;
-// DELO-parabolic (in FP64, whatever the coefficient mode): (w, g) streamed,
-// the linear step's weight and that of the source's curvature.
+// DELO-parabolic (in FP64, whatever the coefficient mode): pairs streamed that
+// give E, the linear step's weight w and that of the source's curvature.
 constexpr int kCoefParabolic = 3;
 
 struct SweepArgs {

@@ -119,7 +119,7 @@ __global__ void ray_setup_kernel(const double *mu_pos, const double *w_pos, int 
 // only for the chunks that have one.  An entry is the pair (E, w) or w alone
 // (the sweep then derives E = 1 - w d).  Padding (frequencies beyond the
 // last, intervals beyond ns - 2) is E = w = 1 (DELO-parabolic, whose entries
-// are the pairs (w, g): w = 1, g = 0): the step leaves I unchanged, and the source beyond the slab is zero.  The rays' quadrature weights and
+// are parabolic_pack's pairs: 1, -0): the step leaves I unchanged, and the source beyond the slab is zero.  The rays' quadrature weights and
 // (kappa, 1 / kappa) are laid out by slot (q_off + (m*nwb + b)*G + slot),
 // zero for padding rays, so the sweep never masks a loaded value.
 // --------------------------------------------------------------------------
@@ -151,15 +151,15 @@ __global__ void coef_build_kernel(int M, const AtmDesc *atm, const BlockDesc *bl
             if (last && !longc) continue;
             const int j = s0 + i;
             double E = 1.0, w = 1.0;
-            const bool curved = fs == RT_FS_DELO_PARABOLIC;  // (w, g) instead of (E, w)
+            const bool curved = fs == RT_FS_DELO_PARABOLIC;  // its own pairs instead of (E, w)
             if (p < at.n_nu && j < at.ns - 1) {
                 const double h = tau[at.doff + j + 1] - tau[at.doff + j], d = kap * h;
                 if (curved)
-                    parabolic_wg(d, h, E, w);
+                    parabolic_pack(d, h, E, w);
                 else
                     step_ew(fs, d, E, w);
             } else if (curved) {
-                w = 0.0;
+                w = -0.0;
             }
             const long long e = at.coef_off + ((long long)m * at.nwb + b) * at.bstride +
                                 (last ? (long long)(at.Leff - 1) * kWave + g * at.nlong + c

@@ -1,5 +1,5 @@
 // rt_sweep_f64_par.hip -- the fused sweep instantiated for double arithmetic,
-// w streamed and E derived.
+// the DELO-parabolic pairs streamed.
 #include "rt_sweep_kernel.h"
 
 namespace rt {

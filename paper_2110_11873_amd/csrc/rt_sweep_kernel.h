@@ -13,7 +13,7 @@
 // current one is computed.  CM: where a step's coefficients (E, w) come from
 // (kCoefPairs: both streamed from the tiles; kCoefW: w streamed, E = 1 - w d
 // derived; kCoefRecompute: both computed from d; kCoefParabolic: w and the
-// curvature weight g streamed, see process), d = kappa dtau the optical step
+// curvature weight g or E streamed, see process), d = kappa dtau the optical step
 // of the interval, kappa = r_p / |mu| per ray, dtau per interval.  Each
 // block writes the 2 ns quadrature sums of its rays to its own slot of
 // `partial`; the finalize pass adds the slots of a slab in block order and
@@ -25,6 +25,7 @@
 
 #include <type_traits>
 
+#include "rt_coef.h"
 #include "rt_finalize.h"
 #include "rt_internal.h"
 
@@ -307,7 +308,7 @@ __device__ __forceinline__ void sweep_rays(const SweepArgs &a, const BlockDesc &
                                            const AtmDesc &at, int wave, int lane, T *sacc,
                                            const T *src) {
     using P2 = typename Pair<T>::type;
-    // one tile entry: the pair (E, w) or (w, g), or w alone
+    // one tile entry: the pair (E, w), that of parabolic_pack, or w alone
     using Ent =
         typename std::conditional<CM == kCoefPairs || CM == kCoefParabolic, P2, T>::type;
     const int ns = at.ns;
@@ -446,14 +447,14 @@ __device__ __forceinline__ void sweep_rays(const SweepArgs &a, const BlockDesc &
             load_pair(rsrc, voff_last + b * bbytes, 0, cn[LE - 1]);
         }
         qn = load_f64(qrsrc, (b * at.G + g) * 8);
-        if constexpr (CM == kCoefW || kCurved) kn.x = load_f64(krsrc, (b * at.G + g) * 16);
-        if constexpr (CM == kCoefRecompute) kn = load_f64x2(krsrc, (b * at.G + g) * 16);
+        if constexpr (CM == kCoefW) kn.x = load_f64(krsrc, (b * at.G + g) * 16);
+        if constexpr (CM == kCoefRecompute || kCurved) kn = load_f64x2(krsrc, (b * at.G + g) * 16);
     };
 
     auto process = [&](Ent (&cn)[LE], double qd, double2 kd) {
         const T q = (T)qd;
         // the steps' (E, w)
-        T Es[LE], ws[LE];
+        T Es[LE], ws[LE], gs[kCurved ? LE : 1];
         if constexpr (CM == kCoefPairs) {
 #pragma unroll
             for (int i = 0; i < LE; ++i) {
@@ -461,15 +462,21 @@ __device__ __forceinline__ void sweep_rays(const SweepArgs &a, const BlockDesc &
                 ws[i] = cn[i].y;
             }
             if (!longc) Es[LE - 1] = ws[LE - 1] = (T)1;  // zero-length step
-        } else if constexpr (CM == kCoefW || kCurved) {
-            const T kap = (T)kd.x;
+        } else if constexpr (kCurved) {
+            if (!longc) {  // zero-length step
+                cn[LE - 1].x = (T)1;
+                cn[LE - 1].y = -(T)0;
+            }
+            const T rk2 = (T)2 * (T)kd.y;
 #pragma unroll
             for (int i = 0; i < LE; ++i) {
-                if constexpr (kCurved)
-                    ws[i] = cn[i].x;
-                else
-                    ws[i] = cn[i];
+                ws[i] = cn[i].x;
+                parabolic_unpack(cn[i].x, cn[i].y, (T)kd.x * dt[i], dt[i], rk2, Es[i], gs[i]);
             }
+        } else if constexpr (CM == kCoefW) {
+            const T kap = (T)kd.x;
+#pragma unroll
+            for (int i = 0; i < LE; ++i) ws[i] = cn[i];
             if (!longc) ws[LE - 1] = (T)1;  // zero-length step (its d is 0)
 #pragma unroll
             for (int i = 0; i < LE; ++i) Es[i] = fma(-ws[i], kap * dt[i], (T)1);
@@ -510,11 +517,10 @@ __device__ __forceinline__ void sweep_rays(const SweepArgs &a, const BlockDesc &
             p0[i] = ws[i] * dl0[i];
             p2[i] = ws[i] * dl2[i];
             if constexpr (kCurved) {
-                const T g = (i + 1 < LE || longc) ? cn[i].y : (T)0;
-                m0[i] = fma(cv0[i], g, -p0[i]);
-                m2[i] = fma(cv2[i], g, -p2[i]);
-                p0[i] = fma(cv0[i + 1], g, p0[i]);
-                p2[i] = fma(cv2[i + 1], g, p2[i]);
+                m0[i] = fma(cv0[i], gs[i], -p0[i]);
+                m2[i] = fma(cv2[i], gs[i], -p2[i]);
+                p0[i] = fma(cv0[i + 1], gs[i], p0[i]);
+                p2[i] = fma(cv2[i + 1], gs[i], p2[i]);
             }
         }
         auto up0 = [&](int i) -> T {

@@ -12,6 +12,7 @@ import pytest
 
 torch = pytest.importorskip("torch")
 
+from oracle import oracle as O  # noqa: E402
 from oracle import redistrib as RO  # noqa: E402
 from paper_2110_11873_amd import binding as B  # noqa: E402
 from paper_2110_11873_amd import workloads as W  # noqa: E402
@@ -29,6 +30,22 @@ def agree(y, ref):
     scale = np.abs(ref).max(axis=1)
     assert scale.min() > 0.0
     assert (np.abs(y - ref).max(axis=1) <= 1e-10 * scale).all(), np.abs(y - ref).max(axis=1) / scale
+
+
+@pytest.mark.parametrize("step", [0.5, 3.0, 20.0, 60.0])
+@pytest.mark.parametrize("slabs", [1, 40])
+def test_parabolic_operator(step, slabs):
+    ns = 12 if step < 60 else 6
+    p = problem("delo_parabolic", ns, step)
+    v = np.zeros(2 * ns)
+    v[0:2] = 1.0, 0.25
+    ref = O.apply(p, v).reshape(ns, 2)
+    many = W.make_slabs([ns] * slabs, [(1.0, 2.0)] * slabs, 8, 21, 1.0, [1e-3] * slabs, [1e-2] * slabs, [0.5] * slabs,
+                        formal_solver="delo_parabolic").with_(tau=np.tile(p.tau, slabs))
+    with B.setup(many) as h:
+        y = h.apply_op(torch.from_numpy(np.tile(v, slabs)).cuda()).cpu().numpy().reshape(slabs, ns, 2)
+    for s in range(slabs):
+        agree(y[s], ref)
 
 
 @pytest.mark.parametrize("fs,step", [("delo_linear", 0.02), ("delo_linear", 2.0), ("delo_linear", 20.0), ("delo_linear", 60.0),
