@@ -424,7 +424,7 @@ static SweepArgs sweep_args(rt_handle *h, const double *in, const double *scale,
     a.mask = mask;
     a.B = h->d_B;
     a.mode = mode;
-    a.part_f32 = fp32 ? 1 : 0;
+    a.part_f32 = partial_fp32(h, fp32) ? 1 : 0;
     return a;
 }
 
@@ -696,6 +696,7 @@ int rt_setup(rt_handle **out, const rt_problem *p, const rt_options *o) {
             h->whole_slabs = true;
         }
     }
+    h->wpd = wpd;
     // Small ones: several blocks per direction, two waves per SIMD in all but
     // at least two batches per wave (below that a block's fixed part costs
     // more than the shorter chain saves).  With about 48 blocks in all

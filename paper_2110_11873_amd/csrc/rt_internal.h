@@ -61,7 +61,7 @@ struct BlockDesc {
     int wb_first;
     int wb_count;
     int slot;
-    int wpd;   // waves per direction: divides the waves of a block
+    int wpd;   // waves per direction: a power of two, at most the waves of a block
     int pad[2];
 };
 
@@ -107,7 +107,7 @@ struct SweepArgs {
     int M;                   // directions |mu|
     int spread;              // log2 of the grid places per block
     int whole;               // 1: every slab is one block, which applies the last step itself
-    int part_f32;            // 1: the partial sums are FP32 (written by an FP32 sweep)
+    int part_f32;            // 1: the partial sums are FP32 (partial_fp32)
 };
 
 // --------------------------------------------------------------------------
@@ -246,6 +246,7 @@ struct rt_handle {
     std::vector<rt::BlockDesc> blk_h;
     int L = 8;                 // chunk length the tiles were built for
     int W = 4;                 // waves per sweep block the plan was made for
+    int wpd = 4;               // waves per direction of the main plan's blocks (the tail plan's: W)
     int NB = 1;                // wave-batches per wave (per block: W * NB)
     int n_blocks = 0;
     int spread = 0;            // log2 of the grid places per block (see rt_setup)
@@ -368,6 +369,11 @@ inline const BlockDesc *plan_blk(const rt_handle *h) {
     return h->plan_tail ? h->d_blk_tail : h->d_blk;
 }
 inline int plan_blocks(const rt_handle *h) { return h->plan_tail ? h->n_blocks_tail : h->n_blocks; }
+// Whether a sweep asked for in FP32 leaves its partial sums in FP32: where a block
+// has one direction (FP64 where it adds several).
+inline bool partial_fp32(const rt_handle *h, bool fp32) {
+    return sweeps_fp32(h, fp32) && (h->plan_tail || h->wpd == h->W);
+}
 inline int plan_nblk_max(const rt_handle *h) {
     return h->plan_tail ? h->nblk_max_tail : h->nblk_max;
 }

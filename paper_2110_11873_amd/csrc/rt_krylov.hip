@@ -184,7 +184,7 @@ struct VecArgs {
     int maxit;
     int max_outer;
     const double *partial;  // the sweep's per-block quadrature sums (float values when part_f32)
-    int part_f32;           // 1: written by an FP32 sweep
+    int part_f32;           // 1: in FP32 (partial_fp32)
     const double4 *Qs;      // per slab: sums over all rays of q, q T1, q (T1^2 + T2^2)
     const double *zin;      // fused Arnoldi step: the sweep's input P^-1 v_j when the
                             // preconditioner is not diagonal (NULL: v_j .* dinv)
@@ -1321,7 +1321,7 @@ struct Driver {
                 ok(apply_sweep(h, vj, h->d_dinv, h->d_cycle, fp32, s));
             }
             VecArgs af = a;
-            af.part_f32 = sweeps_fp32(h, fp32) ? 1 : 0;  // the sweep's partial sums are in its precision
+            af.part_f32 = partial_fp32(h, fp32) ? 1 : 0;
             if (j < 16)
                 hipLaunchKernelGGL(gm_arnoldi_fused_kernel<16>, dim3(h->n_atm), dim3(NTF), 0, s, af, j);
             else

@@ -623,10 +623,14 @@ __device__ __forceinline__ void sweep_rays(const SweepArgs &a, const BlockDesc &
     const double2 tf = a.dirc[m];
     const T t1 = (T)tf.x, t12 = (T)tf.y;
 
-    // block totals of the 2 ns quadrature sums, stored in the sweep's type
-    // (an FP32 sweep's sums are FP32 values: half the bytes, the same numbers)
+    // block totals of the 2 ns quadrature sums.  A direction's sum over its waves
+    // is taken and stored in the sweep's type (an FP32 sweep's sums are FP32
+    // values: half the bytes, the same numbers); directions are added in FP64, by
+    // the finalize pass or, where a block has several, here.
     const int nthr = kWave * W;
     T *mine = reinterpret_cast<T *>(a.partial) + at.part_off + (long long)bd.slot * 2 * ns;
+    double *mine64 = a.partial + at.part_off + (long long)bd.slot * 2 * ns;
+    const bool wide = sizeof(T) == 4 && !a.part_f32;  // FP32 sums stored in FP64
     if (a.rows) {
         // one LDS row per wave, then a fixed-order sum over the rows
         T *row = sacc + (long long)wave * 2 * ns;
@@ -645,23 +649,30 @@ __device__ __forceinline__ void sweep_rays(const SweepArgs &a, const BlockDesc &
             }
         }
         __syncthreads();
+        auto total = [&](int e) {
+            double s = 0.0;
+            T d = (T)0;
+            for (int w = 0; w < W; ++w) {
+                d += sacc[(long long)w * 2 * ns + e];
+                if (sizeof(T) == 4 && ((w + 1) & (wpd - 1)) == 0) {  // a direction is complete
+                    s += (double)d;
+                    d = (T)0;
+                }
+            }
+            return sizeof(T) == 4 ? s : (double)d;
+        };
         if constexpr (LE <= 4) {  // plans of chunk length 4 only: longer bodies keep their registers
             if (a.whole) {  // this block has all of the slab's rays
-                for (int k = threadIdx.x; k < ns; k += nthr) {
-                    T s0 = sacc[2 * k], s2 = sacc[2 * k + 1];
-                    for (int w = 1; w < W; ++w) {
-                        s0 += sacc[(long long)w * 2 * ns + 2 * k];
-                        s2 += sacc[(long long)w * 2 * ns + 2 * k + 1];
-                    }
-                    finalize_point(a, bd.atm, at, k, (double)s0, (double)s2);
-                }
+                for (int k = threadIdx.x; k < ns; k += nthr)
+                    finalize_point(a, bd.atm, at, k, total(2 * k), total(2 * k + 1));
                 return;
             }
         }
         for (int e = threadIdx.x; e < 2 * ns; e += nthr) {
-            T s = sacc[e];
-            for (int w = 1; w < W; ++w) s += sacc[(long long)w * 2 * ns + e];
-            mine[e] = s;
+            if (wide)
+                mine64[e] = total(e);
+            else
+                mine[e] = (T)total(e);
         }
     } else {
         // one shared row, filled wave after wave (fixed order)
@@ -683,8 +694,16 @@ __device__ __forceinline__ void sweep_rays(const SweepArgs &a, const BlockDesc &
                 }
             }
             __syncthreads();
+            if (wide && ((w + 1) & (wpd - 1)) == 0) {  // a direction is complete
+                for (int e = threadIdx.x; e < 2 * ns; e += nthr) {
+                    mine64[e] = (w + 1 == wpd ? 0.0 : mine64[e]) + (double)sacc[e];
+                    sacc[e] = (T)0;
+                }
+                __syncthreads();
+            }
         }
-        for (int e = threadIdx.x; e < 2 * ns; e += nthr) mine[e] = sacc[e];
+        if (!wide)
+            for (int e = threadIdx.x; e < 2 * ns; e += nthr) mine[e] = sacc[e];
     }
 }
 
@@ -717,7 +736,7 @@ __device__ __forceinline__ void dispatch_le(const SweepArgs &a, const BlockDesc 
 // streamed: 4 in FP32 (96 registers; held to 5 it spilled a handful, 61.6 us
 // against 56.8 for 512 slabs of 64 to 512 points) and 3 in FP64 (168
 // registers, about 20 spilled: 120 us, as with two waves and none spilled).
-// DELO-parabolic: 2 (254 registers at chunk length 8, none spilled).  The
+// DELO-parabolic: 2 (249 registers at chunk length 8, none spilled).  The
 // recomputing bodies would spill more.
 template <typename T, int L, int CM>
 struct MinWaves {
