@@ -19,19 +19,20 @@ PKG = os.path.dirname(HERE)
 ROOT = os.path.dirname(PKG)
 INCLUDE = os.path.join(ROOT, "include")
 OUT = os.path.join(PKG, "librt.so")
-SOURCES = ["rt_api.hip", "rt_sweep.hip", "rt_sweep_f32.hip", "rt_sweep_f64.hip",
+SOURCES = ["rt_api.hip", "rt_plan.hip", "rt_sweep.hip", "rt_sweep_f32.hip", "rt_sweep_f64.hip",
            "rt_sweep_f32_w.hip", "rt_sweep_f64_w.hip", "rt_sweep_f32_rc.hip", "rt_sweep_f64_rc.hip",
            "rt_sweep_f64_par.hip", "rt_krylov.hip",
            "rt_assemble.hip", "rt_dense.hip", "rt_field.hip",
            "rt_fieldsolve.hip", "rt_prd.hip", "rt_noalloc.hip"]
 OBJDIR = os.path.join(PKG, "_build")
-# the sources of the sweep's kernels and launchers: their hash is built into
-# the library, and stored launch plans and counter readings are trusted only
-# while it is unchanged
+# the sources of the sweep's kernels, launchers and block plans: their hash is
+# built into the library, and stored launch plans and counter readings are
+# trusted only while it is unchanged
 SWEEP_SOURCES = ["rt_sweep_kernel.h", "rt_finalize.h", "rt_sweep.hip", "rt_sweep_f32.hip",
                  "rt_sweep_f64.hip",
                  "rt_sweep_f32_w.hip", "rt_sweep_f64_w.hip", "rt_sweep_f32_rc.hip",
-                 "rt_sweep_f64_rc.hip", "rt_sweep_f64_par.hip", "rt_coef.h"]
+                 "rt_sweep_f64_rc.hip", "rt_sweep_f64_par.hip", "rt_coef.h",
+                 "rt_plan.hip", "rt_internal.h"]
 
 
 def sweep_source_hash() -> str:

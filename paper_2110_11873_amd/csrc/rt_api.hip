@@ -256,123 +256,6 @@ void resolve_coef_modes(int coef_mode, int *cm64, int *cm32) {
     }
 }
 
-int chunks_for(int ns, int L) {
-    const int x = ns - 1;
-    int C = kMinChunks;
-    while (C < kWave && C * L < x) C <<= 1;
-    return C;
-}
-
-// Chunk length: the largest L whose lane count fills the chip (about two
-// waves per SIMD) -- longer chunks mean fewer scan steps and partial sums --
-// else the shortest, for the most parallelism on small problems.
-int auto_chunk(const std::vector<int> &ns, int rays) {
-    const long long target = 256LL * 4 * kWave * 2;
-    int best = 4;
-    for (int L : {4, 8}) {
-        bool fits = true;
-        long long lanes = 0;
-        for (int n : ns) {
-            const int C = chunks_for(n, L);
-            if ((long long)C * L < n - 1) fits = false;
-            lanes += (long long)rays * C;
-        }
-        if (fits && lanes >= target) best = L;
-    }
-    // a slab deeper than 64 * best intervals needs longer chunks
-    for (int n : ns)
-        while (best < 32 && (long long)kWave * best < n - 1) best *= 2;
-    return best;
-}
-
-// The tile geometry of one slab for a plan of longest chunk L: chunks per
-// ray, chunk length, long chunks, rays per wave-batch, wave-batches per
-// direction and tile entries per wave-batch.
-struct SlabTiles {
-    int C, Leff, nlong, G, nwb, bstride;
-};
-SlabTiles slab_tiles(int ns, int L, int n_nu) {
-    SlabTiles t;
-    t.C = chunks_for(ns, L);
-    t.Leff = chunk_len(ns, t.C, L);
-    // chunk lengths Leff and Leff - 1 tile the ns - 1 intervals exactly
-    // when Leff is ceil((ns - 1) / C); otherwise (lengths rounded up to
-    // a compiled one) all chunks are long and the last ones end past the
-    // slab's bottom in identity steps
-    t.nlong = t.C;
-    if (chunk_len_step(L) == 1) {
-        const int r = (ns - 1) - t.C * (t.Leff - 1);
-        if (r >= 1 && r <= t.C) t.nlong = r;
-    }
-    t.G = kWave / t.C;
-    t.nwb = (n_nu + t.G - 1) / t.G;
-    t.bstride = (t.Leff - 1) * kWave + (t.G * t.nlong + 15) / 16 * 16;
-    return t;
-}
-
-// The sweep addresses the tiles of one (slab, direction) through 32-bit
-// buffer offsets, in entries of up to 16 bytes (FP64 pairs): reject plans
-// whose tiles of one direction exceed 2^31 - 1 bytes.
-int check_tile_range(const std::vector<int> &ns, int L, int n_nu) {
-    for (size_t a = 0; a < ns.size(); ++a) {
-        const SlabTiles t = slab_tiles(ns[a], L, n_nu);
-        if ((long long)t.nwb * t.bstride * 16 > 2147483647LL)
-            return fail(RT_EINVAL, idx("ns", (long long)a) +
-                                       ": the coefficient tiles of one direction exceed 2 GiB "
-                                       "(too many frequencies for this depth grid)");
-    }
-    return RT_OK;
-}
-
-// Frequencies of a slab whose opacity ratios agree to kSameOpac share a formal
-// solution: under complete redistribution the source does not depend on
-// frequency and a ray sees it only through kappa = r_p / |mu|, so their
-// weights w_p phi_p add.  The group's opacity is the weighted mean, which
-// cancels the first-order difference; the second is below 1e-24.  A line
-// profile that is even about its centre halves the rays this way (the two
-// halves of a computed grid differ by up to 1.5e-14); without equal opacities
-// every group is one frequency.  512 slabs of 101 frequencies: the FP64
-// operator takes 250 us with a ray per frequency, 140 us with one per opacity.
-// Strongest opacity first; every slab gets the same number of rays (the largest
-// count), the rest with weight zero.
-constexpr double kSameOpac = 1e-12;
-
-int merge_frequencies(const rt_problem *p, std::vector<double> &opac, std::vector<double> &wphi) {
-    const int n = p->n_nu;
-    std::vector<std::pair<double, double>> f(n);  // (opacity, weight)
-    std::vector<double> kap((size_t)p->n_atm * n), w((size_t)p->n_atm * n);
-    std::vector<int> count(p->n_atm, 0);
-    int most = 0;
-    for (int a = 0; a < p->n_atm; ++a) {
-        const double *op = p->opac + (long long)a * n, *ph = p->phi + (long long)a * n;
-        for (int q = 0; q < n; ++q) f[q] = {op[q], p->w_nu[q] * ph[q]};
-        std::sort(f.begin(), f.end());
-        int g = 0;
-        for (int i = 0; i < n; ++g) {
-            const double first = f[i].first;
-            double sw = 0.0, excess = 0.0;  // of the opacity over the first's
-            for (; i < n && f[i].first - first <= kSameOpac * first; ++i) {
-                sw += f[i].second;
-                excess += f[i].second * (f[i].first - first);
-            }
-            kap[(size_t)a * n + g] = sw > 0.0 ? first + excess / sw : first;
-            w[(size_t)a * n + g] = sw;
-        }
-        count[a] = g;
-        most = std::max(most, g);
-    }
-    opac.resize((size_t)p->n_atm * most);
-    wphi.resize((size_t)p->n_atm * most);
-    for (int a = 0; a < p->n_atm; ++a)
-        for (int g = 0; g < most; ++g) {
-            const bool on = g < count[a];
-            const size_t e = (size_t)a * n + (on ? count[a] - 1 - g : 0);
-            opac[(size_t)a * most + g] = kap[e];
-            wphi[(size_t)a * most + g] = on ? w[e] : 0.0;
-        }
-    return most;
-}
-
 template <typename T>
 int dalloc(T **p, size_t count) {
     *p = nullptr;
@@ -404,8 +287,8 @@ int hip_check(hipError_t e, const char *what) {
 static SweepArgs sweep_args(rt_handle *h, const double *in, const double *scale, double *out,
                             const int *mask, bool fp32, int mode) {
     SweepArgs a{};
-    a.atm = plan_atm(h);
-    a.blk = plan_blk(h);
+    a.atm = plan_of(h).d_atm;
+    a.blk = plan_of(h).d_blk;
     const int cm = coef_mode_of(h, fp32);
     a.coef = cm == kCoefParabolic ? (const void *)h->d_coef64
              : cm == kCoefPairs ? (fp32 ? (const void *)h->d_coef32 : (const void *)h->d_coef64)
@@ -432,12 +315,12 @@ hipError_t apply_sweep(rt_handle *h, const double *in, const double *scale, cons
                        bool fp32, hipStream_t s) {
     fp32 = sweeps_fp32(h, fp32);
     SweepArgs a = sweep_args(h, in, scale, nullptr, mask, fp32, 0);
-    a.spread = h->plan_tail ? 0 : h->spread;
+    a.spread = plan_of(h).spread;
     int W;
     bool pf;
     sweep_config(h, fp32, &W, &pf);
-    return launch_sweep(h->L, W, pf, fp32, coef_mode_of(h, fp32), a, plan_blocks(h), h->ns_max,
-                        s);
+    return launch_sweep(h->L, W, pf, fp32, coef_mode_of(h, fp32), a, plan_of(h).n_blocks,
+                        h->ns_max, s);
 }
 
 hipError_t apply_operator_into(rt_handle *h, const double *in, double *out, double *partial,
@@ -447,25 +330,25 @@ hipError_t apply_operator_into(rt_handle *h, const double *in, double *out, doub
     int W;
     bool pf;
     sweep_config(h, false, &W, &pf);
-    a.whole = h->whole_slabs ? 1 : 0;
-    hipError_t e = launch_sweep(h->L, W, pf, false, coef_mode_of(h, false), a, plan_blocks(h),
-                                h->ns_max, s);
+    a.whole = plan_of(h).whole ? 1 : 0;
+    hipError_t e = launch_sweep(h->L, W, pf, false, coef_mode_of(h, false), a,
+                                plan_of(h).n_blocks, h->ns_max, s);
     if (e != hipSuccess || a.whole) return e;
-    return launch_finalize(a, h->n_atm, h->ns_max, plan_nblk_max(h), s);
+    return launch_finalize(a, h->n_atm, h->ns_max, plan_of(h).nblk_max, s);
 }
 
 hipError_t apply_operator(rt_handle *h, const double *in, const double *scale, double *out,
                           const int *mask, bool fp32, int mode, hipStream_t s) {
     fp32 = sweeps_fp32(h, fp32);
     SweepArgs a = sweep_args(h, in, scale, out, mask, fp32, mode);
-    a.whole = h->whole_slabs && !h->plan_tail ? 1 : 0;
+    a.whole = plan_of(h).whole ? 1 : 0;
     int W;
     bool pf;
     sweep_config(h, fp32, &W, &pf);
-    hipError_t e = launch_sweep(h->L, W, pf, fp32, coef_mode_of(h, fp32), a, plan_blocks(h),
+    hipError_t e = launch_sweep(h->L, W, pf, fp32, coef_mode_of(h, fp32), a, plan_of(h).n_blocks,
                                 h->ns_max, s);
     if (e != hipSuccess || a.whole) return e;
-    return launch_finalize(a, h->n_atm, h->ns_max, plan_nblk_max(h), s);
+    return launch_finalize(a, h->n_atm, h->ns_max, plan_of(h).nblk_max, s);
 }
 
 void clear_graphs(rt_handle *h) {
@@ -638,209 +521,11 @@ int rt_setup(rt_handle **out, const rt_problem *p, const rt_options *o) {
     h->ns_total = acc;
     h->n_unk = 2 * acc;
 
-    // ---- plan: chunks, wave-batches, blocks, tiles, partial sums
     std::vector<double> opac_c, wphi_c;
-    h->nc = merge_frequencies(p, opac_c, wphi_c);
-    const int rays = h->M * h->nc;
-    h->L = opt.chunk ? opt.chunk : auto_chunk(h->ns, rays);
-    for (int n : h->ns)
-        if ((long long)kWave * h->L < n - 1) {
-            delete h;
-            return fail(RT_EINVAL, "options.chunk too short for ns (need 64 * chunk >= ns - 1)");
-        }
-    // the same test as rt_validate, which does not look for equal opacities
-    if ((rc = check_tile_range(h->ns, opt.chunk ? opt.chunk : auto_chunk(h->ns, h->M * h->n_nu),
-                               h->n_nu)) != RT_OK) {
+    if ((rc = plan_sweeps(h, p, opac_c, wphi_c)) != RT_OK) {
         delete h;
         return rc;
     }
-    long long coef = 0, part = 0, qt = 0, dense = 0, ew = 0, part_t = 0;
-    int blk = 0, blk_t = 0;
-    h->nblk_max = h->nblk_max_tail = 0;
-    std::vector<AtmDesc> atm_t(h->n_atm);
-    std::vector<BlockDesc> blk_t_h;
-    // Waves per block, waves per direction and wave-batches per wave.
-    //
-    // Four waves per block; eight for a single slab, whose Arnoldi step adds up
-    // the blocks' sums in one workgroup (200 points, 20 x 101 rays: GMRES 1.55
-    // -> 1.51 ms, the operator alone the same).  Eight are compiled for chunks
-    // up to 8 only: longer ones take four, also where the caller asked for eight
-    // and left the chunk to the slabs' depths.
-    h->W = opt.sweep_waves ? opt.sweep_waves : h->n_atm == 1 ? 8 : 4;
-    if (h->L > 8) h->W = 4;
-    const long long dirs_total = (long long)h->n_atm * h->M;
-    long long batches_total = 0;
-    for (int n : h->ns) batches_total += (long long)h->M * slab_tiles(n, h->L, h->nc).nwb;
-    // Big batches: the fewest waves per direction (a power of two) that still
-    // give five waves per SIMD, so that what a wave does once -- sources,
-    // depth steps, the sum over its rays -- is shared by more of its ray
-    // batches.  FP64 / FP32 operator, slabs of 64 to 512 points, 16 directions,
-    // 101 frequencies, us with 4, 2 and 1 waves per direction: 256 slabs
-    // 65 / 35, 61 / 35, 85 / 50; 320 slabs 89 / 41, 85 / 39, 100 / 52; 512
-    // slabs 136 / 66, 126 / 59, 124 / 69; 1024 slabs 263 / 140, 242 / 124,
-    // 233 / 124.
-    int wpd = h->W;
-    if (opt.wave_batches == 0)
-        while (wpd > 1 && dirs_total * (wpd / 2) >= 5 * 4 * 256) wpd /= 2;
-    // One small slab: all of its directions in one block if that leaves a wave
-    // at most four batches; the block then ends the operator itself and the
-    // finalize launch goes (40 points, 8 x 21 rays: 9.8 -> 7.2 us back to back).
-    {
-        int w1 = h->W;
-        while (w1 > 1 && (h->W / w1) < h->M) w1 /= 2;
-        const int nwb = slab_tiles(h->ns[0], h->L, h->nc).nwb;
-        if (opt.wave_batches == 0 && h->n_atm == 1 && h->L == 4 && h->W / w1 >= h->M &&
-            (nwb + w1 - 1) / w1 <= 4 &&
-            (size_t)(h->W + 1) * 2 * h->ns_max * sizeof(double) <= (size_t)kSweepLdsBudget) {
-            wpd = w1;
-            h->whole_slabs = true;
-        }
-    }
-    h->wpd = wpd;
-    // Small ones: several blocks per direction, two waves per SIMD in all but
-    // at least two batches per wave (below that a block's fixed part costs
-    // more than the shorter chain saves).  With about 48 blocks in all
-    // instead: one 1024-point slab 30.8 -> 24.6 us FP64, 21.6 -> 16.1 FP32; 8
-    // slabs 16.7 -> 10.4; 32 slabs 22.9 -> 17.7; 64 slabs 24.8 -> 23.0.
-    constexpr long long kFillWaves = 2 * 4 * 256;
-    const int nb_fill = (int)std::max<long long>(2, (batches_total + kFillWaves - 1) / kFillWaves);
-    h->atm_h.resize(h->n_atm);
-    for (int a = 0; a < h->n_atm; ++a) {
-        AtmDesc d{};
-        d.ns = h->ns[a];
-        d.doff = h->doff[a];
-        const SlabTiles t = slab_tiles(d.ns, h->L, h->nc);
-        d.C = t.C;
-        d.Leff = t.Leff;
-        d.nlong = t.nlong;
-        d.G = t.G;
-        d.n_nu = h->nc;
-        d.nwb = t.nwb;
-        d.bstride = t.bstride;
-        d.ray_off = a * rays;
-        int nb = std::min(std::min(nb_fill, 32), (d.nwb + wpd - 1) / wpd);
-        if (wpd < h->W || h->whole_slabs) nb = (d.nwb + wpd - 1) / wpd;
-        if (opt.wave_batches > 0) nb = opt.wave_batches;
-        const int dpb = h->W / wpd;  // directions per block
-        const int dgroups = (h->M + dpb - 1) / dpb;
-        const int wb_per_block = wpd * nb;
-        const int blk_per_dir = (d.nwb + wb_per_block - 1) / wb_per_block;
-        d.nblk = dgroups * blk_per_dir;
-        d.blk_first = blk;
-        d.coef_off = coef;
-        d.part_off = part;
-        d.q_off = qt;
-        d.a_off = dense;
-        d.ew_off = ew;
-        dense += 4LL * d.ns * d.ns;
-        ew += (long long)(d.ns - 1) * rays;
-        d.eps = p->eps[a];
-        d.xi = 1.0 - p->eps[a];
-        d.W2 = p->W2[a];
-        d.Ibot = p->I_bot ? p->I_bot[a] : (p->B ? p->B[d.doff + d.ns - 1] : 1.0);
-        for (int mg = 0; mg < dgroups; ++mg) {
-            for (int bb = 0; bb < blk_per_dir; ++bb) {
-                BlockDesc bd{};
-                bd.atm = a;
-                bd.m = mg * dpb;
-                bd.wb_first = bb * wb_per_block;
-                bd.wb_count = std::min(wb_per_block, d.nwb - bd.wb_first);
-                bd.slot = mg * blk_per_dir + bb;
-                bd.wpd = wpd;
-                h->blk_h.push_back(bd);
-            }
-        }
-        h->NB = nb;
-        // the tail plan: the same tiles, at most kTailWb wave-batches per
-        // wave (a plan the caller fixed is kept for every cycle)
-        {
-            const int nbt = opt.wave_batches > 0 ? nb : std::min(nb, kTailWb);
-            const int wbt = h->W * nbt;
-            const int bpd = (d.nwb + wbt - 1) / wbt;
-            AtmDesc dt = d;
-            dt.nblk = h->M * bpd;
-            dt.blk_first = blk_t;
-            dt.part_off = part_t;
-            for (int m = 0; m < h->M; ++m) {
-                for (int bb = 0; bb < bpd; ++bb) {
-                    BlockDesc bd{};
-                    bd.atm = a;
-                    bd.m = m;
-                    bd.wb_first = bb * wbt;
-                    bd.wb_count = std::min(wbt, d.nwb - bd.wb_first);
-                    bd.slot = m * bpd + bb;
-                    bd.wpd = h->W;
-                    blk_t_h.push_back(bd);
-                }
-            }
-            blk_t += dt.nblk;
-            part_t += (long long)dt.nblk * 2 * d.ns;
-            atm_t[a] = dt;
-        }
-        blk += d.nblk;
-        h->nblk_max = std::max(h->nblk_max, d.nblk);
-        h->nblk_max_tail = std::max(h->nblk_max_tail, atm_t[a].nblk);
-        coef += (long long)h->M * d.nwb * d.bstride;
-        qt += (long long)h->M * d.nwb * d.G;
-        part += (long long)d.nblk * 2 * d.ns;
-        h->atm_h[a] = d;
-    }
-    h->n_blocks = blk;
-    // longest blocks first (work ~ wave-batches x chunk length, the same
-    // lane count per batch); ties keep slab order
-    auto order_blocks = [&](std::vector<BlockDesc> &list) {
-        std::stable_sort(list.begin(), list.end(), [&](const BlockDesc &x, const BlockDesc &y) {
-            return (long long)x.wb_count * h->atm_h[x.atm].Leff >
-                   (long long)y.wb_count * h->atm_h[y.atm].Leff;
-        });
-        {
-            // XCD-aware order: workgroups are handed to the 8 XCDs in turn by
-            // index, and the blocks of one slab stage the same sources, so each
-            // slab's run of blocks goes to one XCD (indices 8 apart, one L2) and
-            // consecutive runs to consecutive XCDs -- the longest-first order
-            // kept per group of 8 runs.  Applied when the runs fill the XCDs
-            // evenly (equal-size runs, a multiple of 8 of them).
-            constexpr int kXcd = 8;
-            std::vector<std::vector<BlockDesc>> q(kXcd);
-            size_t i = 0;
-            int run = 0;
-            while (i < list.size()) {
-                size_t j = i;
-                while (j < list.size() && list[j].atm == list[i].atm) ++j;
-                for (size_t k = i; k < j; ++k) q[run % kXcd].push_back(list[k]);
-                ++run;
-                i = j;
-            }
-            bool even = true;
-            for (int x = 1; x < kXcd; ++x) even = even && q[x].size() == q[0].size();
-            if (even && !q[0].empty()) {
-                std::vector<BlockDesc> out;
-                out.reserve(list.size());
-                for (size_t k = 0; k < q[0].size(); ++k)
-                    for (int x = 0; x < kXcd; ++x) out.push_back(q[x][k]);
-                list.swap(out);
-            }
-        }
-    };
-    order_blocks(h->blk_h);
-    // A single slab of few blocks: all of them on one XCD (workgroups go to
-    // the 8 in turn: every eighth place of the grid, the others empty), so that
-    // the workgroup that reads their sums, the first of its grid, finds them in
-    // its L2: 200 points, 20 x 101 rays, 40 blocks of 8 waves: GMRES 1.51 ->
-    // 1.42 ms.  The operator alone ends in a pass over all XCDs and keeps them.
-    if (h->n_atm == 1 && h->n_blocks > 1 && h->n_blocks <= 64 && h->ns_max <= 512) h->spread = 3;
-    // the tail plan only where it differs
-    const bool tail_plan = blk_t != blk;
-    if (tail_plan) {
-        order_blocks(blk_t_h);
-        h->n_blocks_tail = blk_t;
-    }
-    h->n_qt = qt;
-    h->n_pairs = coef;
-    h->n_partial = tail_plan ? std::max(part, part_t) : part;
-    h->n_partial_main = part;
-    h->n_dense = dense;
-    h->n_ew = ew;
 
     // ---- device memory
     std::vector<int> pt_atm(acc);
@@ -909,14 +594,13 @@ int rt_setup(rt_handle **out, const rt_problem *p, const rt_options *o) {
         put(&h->d_opac_c, opac_c.data(), nmerged);
         put(&h->d_wphi_c, wphi_c.data(), nmerged);
         put(&h->d_pt_atm, pt_atm.data(), acc);
-        put(&h->d_atm, h->atm_h.data(), h->n_atm);
-        put(&h->d_blk, h->blk_h.data(), h->n_blocks);
+        for (SweepPlan *pl : {&h->main, &h->tail}) {
+            if (!pl->n_blocks) continue;
+            put(&pl->d_atm, pl->atm.data(), pl->atm.size());
+            put(&pl->d_blk, pl->blk.data(), pl->blk.size());
+        }
         put(&h->d_tri_order, order.data(), h->n_atm);
         if (derive) put(&h->d_dtau, dtau.data(), acc);
-        if (tail_plan) {
-            put(&h->d_atm_tail, atm_t.data(), h->n_atm);
-            put(&h->d_blk_tail, blk_t_h.data(), h->n_blocks_tail);
-        }
         char *base;
         RT_TRY(dalloc(&base, total));
         for (const Part &q : parts) *q.dst = base + q.off;
@@ -928,6 +612,8 @@ int rt_setup(rt_handle **out, const rt_problem *p, const rt_options *o) {
             for (const Part &q : parts) RT_TRY(h2d(base + q.off, (const char *)q.src, q.bytes));
         }
     }
+    h->d_atm = h->main.d_atm;
+    const int rays = h->M * h->nc;
     RT_TRY(dalloc(&h->d_fsig, (size_t)2 * acc));
     RT_TRY(dalloc(&h->d_rayc, (size_t)h->n_atm * rays));
     RT_TRY(dalloc(&h->d_rayc_nu, nphi * h->M));
@@ -952,7 +638,7 @@ int rt_setup(rt_handle **out, const rt_problem *p, const rt_options *o) {
     RT_TRY(hip_check(launch_ray_setup(h->n_atm, h->d_mu_pos, h->d_w_pos, h->M, h->d_wphi_c, h->nc,
                                       h->normalize, h->d_rayc, h->d_dirc, h->d_Qs, s),
                      "ray setup launch"));
-    RT_TRY(hip_check(launch_coef_build(h->n_blocks, h->W, h->M, h->d_atm, h->d_blk, h->d_tau,
+    RT_TRY(hip_check(launch_coef_build(h->main.n_blocks, h->W, h->M, h->d_atm, h->main.d_blk, h->d_tau,
                                        h->d_opac_c, h->d_mu_pos, h->fs, h->d_rayc, h->d_coef64,
                                        h->d_coef32, h->d_w64, h->d_w32, h->d_qt, h->d_kt, s),
                      "coefficient launch"));
@@ -1039,7 +725,7 @@ int rt_plan_info(const rt_handle *h, int *chunk_L, int *n_blocks, long long *n_p
                  long long *n_intervals) {
     if (!h) return fail(RT_EINVAL, "NULL handle");
     if (chunk_L) *chunk_L = h->L;
-    if (n_blocks) *n_blocks = h->n_blocks;
+    if (n_blocks) *n_blocks = h->main.n_blocks;
     if (n_pairs) *n_pairs = h->n_pairs;
     if (n_intervals) {
         long long s = 0;

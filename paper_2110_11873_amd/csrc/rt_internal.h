@@ -129,6 +129,20 @@ __host__ __device__ inline int lane_slot(int lane, int C) {
 }
 
 
+// A block list of the sweep and the slab table it goes with (rt_plan.hip).
+struct SweepPlan {
+    int n_blocks = 0;         // 0: no such plan
+    int nblk_max = 0;         // most blocks of one slab
+    int wpd = 0;              // waves per direction
+    int spread = 0;           // log2 of the grid places per block, where the Arnoldi step reads the sums
+    bool whole = false;       // every slab is one block: no finalize pass
+    long long n_partial = 0;  // partial sums of its blocks
+    std::vector<AtmDesc> atm;
+    std::vector<BlockDesc> blk;
+    AtmDesc *d_atm = nullptr;  // on the device
+    BlockDesc *d_blk = nullptr;
+};
+
 // Chunk counts of a plan: powers of two from kMinChunks to 64 (short slabs
 // get identity-padded chunks rather than fewer of them, so the sweep has one
 // lane layout per chunk count it is compiled for).
@@ -187,6 +201,13 @@ hipError_t launch_diag(int npts, const int *pt_atm, const AtmDesc *atm, const do
                        const double *opac, const double *mu_pos, const RayConst *rayc, int M,
                        int n_nu, int fs, double *diag, double *dinv, hipStream_t s);
 bool sweep_chunk_supported(int L, bool fp32);
+// The automatic chunk length, and the test that the tiles of a plan can be
+// addressed (rt_plan.hip).
+int auto_chunk(const std::vector<int> &ns, int rays);
+int check_tile_range(const std::vector<int> &ns, int L, int n_nu);
+// The handle's rays, tiles and block lists; the merged rays' opacities and weights.
+int plan_sweeps(rt_handle *h, const rt_problem *p, std::vector<double> &opac_c,
+                std::vector<double> &wphi_c);
 // Chunk length of a slab of ns points split into C chunks, for a plan of
 // longest chunk L: ceil((ns - 1) / C) rounded up to a length the sweep is
 // compiled for.
@@ -242,22 +263,13 @@ struct rt_handle {
     int n_unk = 0, ns_total = 0, ns_max = 0;
     rt_options opt{};
     std::vector<int> ns, doff;
-    std::vector<rt::AtmDesc> atm_h;
-    std::vector<rt::BlockDesc> blk_h;
     int L = 8;                 // chunk length the tiles were built for
     int W = 4;                 // waves per sweep block the plan was made for
-    int wpd = 4;               // waves per direction of the main plan's blocks (the tail plan's: W)
-    int NB = 1;                // wave-batches per wave (per block: W * NB)
-    int n_blocks = 0;
-    int spread = 0;            // log2 of the grid places per block (see rt_setup)
-    bool whole_slabs = false;  // every slab is one block: no finalize pass
-    int nblk_max = 0, nblk_max_tail = 0;  // most blocks of one slab, per plan
     long long n_pairs = 0, n_partial = 0;
-    long long n_partial_main = 0;  // partial sums of the main plan's blocks
-    // the tail plan over the same coefficient tiles (none when it would equal
-    // the main plan); plan_tail selects it for the sweeps, their finalize pass
-    // and the fused Arnoldi step, which all read the slab table it points to
-    int n_blocks_tail = 0;
+    // the main plan, and the tail plan over the same coefficient tiles (none when
+    // it would equal the main plan); plan_tail selects it for the sweeps, their
+    // finalize pass and the fused Arnoldi step
+    rt::SweepPlan main, tail;
     bool plan_tail = false;
 
     // device copies of the problem
@@ -269,10 +281,7 @@ struct rt_handle {
     int nc = 0;
     double *d_opac_c = nullptr, *d_wphi_c = nullptr;
     int *d_pt_atm = nullptr;
-    rt::AtmDesc *d_atm = nullptr;
-    rt::BlockDesc *d_blk = nullptr;
-    rt::AtmDesc *d_atm_tail = nullptr;  // nblk, blk_first, part_off of the tail plan
-    rt::BlockDesc *d_blk_tail = nullptr;
+    rt::AtmDesc *d_atm = nullptr;  // the main plan's slab table
     rt::RayConst *d_rayc = nullptr;     // per merged ray m nc + p of each slab (ray_off)
     rt::RayConst *d_rayc_nu = nullptr;  // per (|mu|, frequency) m n_nu + p of each slab
     double *d_qt = nullptr;       // tile-ordered, zero-padded quadrature weights
@@ -361,21 +370,12 @@ struct rt_handle {
 
 namespace rt {
 
-// The slab table, block list and block count of the plan the sweeps use now.
-inline const AtmDesc *plan_atm(const rt_handle *h) {
-    return h->plan_tail ? h->d_atm_tail : h->d_atm;
-}
-inline const BlockDesc *plan_blk(const rt_handle *h) {
-    return h->plan_tail ? h->d_blk_tail : h->d_blk;
-}
-inline int plan_blocks(const rt_handle *h) { return h->plan_tail ? h->n_blocks_tail : h->n_blocks; }
+// The plan the sweeps use now.
+inline const SweepPlan &plan_of(const rt_handle *h) { return h->plan_tail ? h->tail : h->main; }
 // Whether a sweep asked for in FP32 leaves its partial sums in FP32: where a block
 // has one direction (FP64 where it adds several).
 inline bool partial_fp32(const rt_handle *h, bool fp32) {
-    return sweeps_fp32(h, fp32) && (h->plan_tail || h->wpd == h->W);
-}
-inline int plan_nblk_max(const rt_handle *h) {
-    return h->plan_tail ? h->nblk_max_tail : h->nblk_max;
+    return sweeps_fp32(h, fp32) && plan_of(h).wpd == h->W;
 }
 
 // sigma_out = A (scale .* sigma_in) for the slabs whose mask is set (all if
@@ -383,7 +383,7 @@ inline int plan_nblk_max(const rt_handle *h) {
 hipError_t apply_operator(rt_handle *h, const double *in, const double *scale, double *out,
                           const int *mask, bool fp32, int mode, hipStream_t s);
 // sigma_out = A sigma_in in FP64 (rt_apply_op) with the per-block partial
-// quadrature sums in `partial` (at least n_partial_main doubles) instead of
+// quadrature sums in `partial` (at least main.n_partial doubles) instead of
 // the handle's buffer; main plan, no scaling, no mask.
 hipError_t apply_operator_into(rt_handle *h, const double *in, double *out, double *partial,
                                hipStream_t s);

@@ -1435,8 +1435,8 @@ struct Driver {
             // a cycle that starts with few slabs still iterating sweeps with
             // the tail plan; the choice is made here only, so eager launches
             // and graph replays take the same plan in every cycle
-            h->plan_tail = h->n_blocks_tail > 0 && act <= kTailSlabs;
-            a.atm = plan_atm(h);
+            h->plan_tail = h->tail.n_blocks > 0 && act <= kTailSlabs;
+            a.atm = plan_of(h).d_atm;
             key.back() = h->plan_tail ? 1 : 0;
             if (h->opt.graphs) {
                 graph(key, [&]() {

@@ -59,8 +59,8 @@ extern "C" int rt_apply_op_noalloc(rt_handle *h, const double *sigma_in, double 
         return fail(RT_EINVAL, "vectors must be 16-byte aligned");
     if (h->fs == RT_FS_DELO_PARABOLIC)
         return fail(RT_EINVAL, "rt_apply_op_noalloc supports the two-point formal solvers only");
-    if (h->n_partial_main > kScratchDoubles)
-        return fail(RT_EINVAL, "the handle's sweep needs " + std::to_string(h->n_partial_main) +
+    if (h->main.n_partial > kScratchDoubles)
+        return fail(RT_EINVAL, "the handle's sweep needs " + std::to_string(h->main.n_partial) +
                                    " partial sums, more than the " +
                                    std::to_string(kScratchDoubles) +
                                    " the allocation-free operator holds (RT_NOALLOC_MAX_PARTIAL)");
