@@ -219,10 +219,16 @@ int plan_sweeps(rt_handle *h, const rt_problem *p, std::vector<double> &opac_c,
     //
     // Four waves per block; eight for a single slab, whose Arnoldi step adds up
     // the blocks' sums in one workgroup (200 points, 20 x 101 rays: GMRES 1.55
-    // -> 1.51 ms, the operator alone the same).  Eight are compiled for chunks
-    // up to 8 only: longer ones take four, also where the caller asked for eight
-    // and left the chunk to the slabs' depths.
-    h->W = opt.sweep_waves ? opt.sweep_waves : h->n_atm == 1 ? 8 : 4;
+    // -> 1.51 ms, the operator alone the same), as long as their sums fit a row
+    // each: eight waves that fill a shared row in turn take longer than four with
+    // rows (512 points, 16 x 64 rays: operator 20.2 us against 11.8, GMRES 4.53
+    // ms against 3.26).  Eight are compiled for chunks up to 8 only: longer ones
+    // take four, also where the caller asked for eight and left the chunk to the
+    // slabs' depths.
+    const auto rows_fit = [&](int waves) {
+        return (size_t)(waves + 1) * 2 * h->ns_max * sizeof(double) <= (size_t)kSweepLdsBudget;
+    };
+    h->W = opt.sweep_waves ? opt.sweep_waves : h->n_atm == 1 && rows_fit(8) ? 8 : 4;
     if (h->L > 8) h->W = 4;
     const long long dirs_total = (long long)h->n_atm * h->M;
     long long batches_total = 0;
@@ -247,8 +253,7 @@ int plan_sweeps(rt_handle *h, const rt_problem *p, std::vector<double> &opac_c,
         while (w1 > 1 && (h->W / w1) < h->M) w1 /= 2;
         const int nwb = slab_tiles(h->ns[0], h->L, h->nc).nwb;
         if (opt.wave_batches == 0 && h->n_atm == 1 && h->L == 4 && h->W / w1 >= h->M &&
-            (nwb + w1 - 1) / w1 <= 4 &&
-            (size_t)(h->W + 1) * 2 * h->ns_max * sizeof(double) <= (size_t)kSweepLdsBudget) {
+            (nwb + w1 - 1) / w1 <= 4 && rows_fit(h->W)) {
             wpd = w1;
             whole = true;
         }

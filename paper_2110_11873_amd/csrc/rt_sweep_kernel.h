@@ -804,6 +804,7 @@ hipError_t launch(const SweepArgs &a, int W, bool pf, int nblocks, int ns_max, h
     if constexpr (L <= 8) {
         if (W == 8) return launch_tw<T, L, 8, CM>(a, pf, nblocks, ns_max, s);
     }
+    if (W != 4) return hipErrorInvalidValue;  // the block list was made for W waves
     return launch_tw<T, L, 4, CM>(a, pf, nblocks, ns_max, s);
 }
 
