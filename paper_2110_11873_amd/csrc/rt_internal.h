@@ -148,9 +148,17 @@ struct SweepPlan {
 // lane layout per chunk count it is compiled for).
 constexpr int kMinChunks = 8;
 // The tail plan: GMRES cycles that start with at most kTailSlabs slabs still
-// iterating sweep with at most kTailWb wave-batches per wave, so those slabs
+// iterating sweep with at most kTailWb wave-batches per wave, so that those slabs
 // spread over more workgroups (the main plan, made for the whole batch, gives
-// a long slab one workgroup per direction).
+// a long slab one workgroup per direction), and with at least kSolveWb, as the
+// Arnoldi step reads every workgroup's sums: the main plan of a few slabs, made
+// for the operator alone, has two.  GMRES, us a step, 2 and 4 batches per wave,
+// slabs of 64 to 512 points, 16 x 101 rays: without equal opacities 2 slabs 26.6
+// and 24.2 (mixed 28.7 and 26.0), 4 slabs 26.3 and 23.6 (32.0 and 26.2), 8 slabs
+// 27.9 and 24.4 (31.2 and 27.1); with, 4 slabs 22.0 and 21.6 (26.7 and 26.2).
+// The operator alone takes 10.0 and 11.8 us on 2 slabs.
+constexpr int kSolveWb = 4;
+constexpr int kOneXcd = 40;  // blocks of a single slab that one XCD takes
 constexpr int kTailSlabs = 128;
 constexpr int kTailWb = 8;
 

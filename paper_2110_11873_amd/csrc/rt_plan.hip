@@ -265,6 +265,10 @@ int plan_sweeps(rt_handle *h, const rt_problem *p, std::vector<double> &opac_c,
     // slabs 16.7 -> 10.4; 32 slabs 22.9 -> 17.7; 64 slabs 24.8 -> 23.0.
     constexpr long long kFillWaves = 2 * 4 * 256;
     const int nb_fill = (int)std::max<long long>(2, (batches_total + kFillWaves - 1) / kFillWaves);
+    // The plan that the Arnoldi step reads: at least kSolveWb batches per wave,
+    // but two where a single slab then has no more than kOneXcd blocks.
+    const int slab_blocks = h->M * ((slab_tiles(h->ns_max, h->L, h->nc).nwb + 2 * h->W - 1) / (2 * h->W));
+    const int solve_wb = h->n_atm == 1 && slab_blocks <= kOneXcd ? 2 : kSolveWb;
     std::vector<AtmDesc> atm(h->n_atm);
     std::vector<int> nb(h->n_atm), nb_tail(h->n_atm);
     for (int a = 0; a < h->n_atm; ++a) {
@@ -296,20 +300,24 @@ int plan_sweeps(rt_handle *h, const rt_problem *p, std::vector<double> &opac_c,
         if (wpd < h->W || whole) nb[a] = (d.nwb + wpd - 1) / wpd;
         if (opt.wave_batches > 0) nb[a] = opt.wave_batches;
         // a plan the caller fixed is kept for every cycle
-        nb_tail[a] = opt.wave_batches > 0 ? nb[a] : std::min(nb[a], kTailWb);
+        nb_tail[a] = opt.wave_batches > 0 ? nb[a] : std::min(std::max(nb[a], solve_wb), kTailWb);
     }
     h->main = make_plan(atm, h->M, h->W, wpd, nb);
     h->main.whole = whole;
-    // A single slab of few blocks: all of them on one XCD (workgroups go to
-    // the 8 in turn: every eighth place of the grid, the others empty), so that
-    // the workgroup that reads their sums, the first of its grid, finds them in
-    // its L2: 200 points, 20 x 101 rays, 40 blocks of 8 waves: GMRES 1.51 ->
-    // 1.42 ms.  The operator alone ends in a pass over all XCDs and keeps them.
-    if (h->n_atm == 1 && h->main.n_blocks > 1 && h->main.n_blocks <= 64 && h->ns_max <= 512)
-        h->main.spread = 3;
     // the tail plan, over the same tiles, only where it differs
     SweepPlan tail = make_plan(atm, h->M, h->W, h->W, nb_tail);
     if (tail.n_blocks != h->main.n_blocks) h->tail = std::move(tail);
+    // A single slab of few blocks: all of them on one XCD (workgroups go to
+    // the 8 in turn: every eighth place of the grid, the others empty), so that
+    // the workgroup that reads their sums, the first of its grid, finds them in
+    // its L2: 200 points, 20 x 101 rays, 40 blocks of 8 waves, 20.9 -> 19.8 us a
+    // GMRES step.  More blocks take turns on its 32 CUs: 64 of 8 waves (400
+    // points, 32 x 201 rays) 26.5 us on all XCDs, 34.8 on one; 56 (283 points, 16 x
+    // 101 distinct rays) 23.1 and 25.8, or 22.1 as 32 blocks of four batches per
+    // wave on one.  The operator alone ends in a pass over all XCDs and keeps them.
+    SweepPlan &solve = h->tail.n_blocks ? h->tail : h->main;
+    if (h->n_atm == 1 && solve.n_blocks > 1 && solve.n_blocks <= kOneXcd && h->ns_max <= 512)
+        solve.spread = 3;
     h->n_partial = std::max(h->main.n_partial, h->tail.n_partial);
     return RT_OK;
 }
