@@ -230,21 +230,8 @@ int plan_sweeps(rt_handle *h, const rt_problem *p, std::vector<double> &opac_c,
     };
     h->W = opt.sweep_waves ? opt.sweep_waves : h->n_atm == 1 && rows_fit(8) ? 8 : 4;
     if (h->L > 8) h->W = 4;
-    const long long dirs_total = (long long)h->n_atm * h->M;
-    long long batches_total = 0;
-    for (int n : h->ns) batches_total += (long long)h->M * slab_tiles(n, h->L, h->nc).nwb;
-    // Big batches: the fewest waves per direction (a power of two) that still
-    // give five waves per SIMD, so that what a wave does once -- sources,
-    // depth steps, the sum over its rays -- is shared by more of its ray
-    // batches.  FP64 / FP32 operator, slabs of 64 to 512 points, 16 directions,
-    // 101 frequencies, us with 4, 2 and 1 waves per direction: 256 slabs
-    // 65 / 35, 61 / 35, 85 / 50; 320 slabs 89 / 41, 85 / 39, 100 / 52; 512
-    // slabs 136 / 66, 126 / 59, 124 / 69; 1024 slabs 263 / 140, 242 / 124,
-    // 233 / 124.
     int wpd = h->W;
     bool whole = false;
-    if (opt.wave_batches == 0)
-        while (wpd > 1 && dirs_total * (wpd / 2) >= 5 * 4 * 256) wpd /= 2;
     // One small slab: all of its directions in one block if that leaves a wave
     // at most four batches; the block then ends the operator itself and the
     // finalize launch goes (40 points, 8 x 21 rays: 9.8 -> 7.2 us back to back).
@@ -258,6 +245,23 @@ int plan_sweeps(rt_handle *h, const rt_problem *p, std::vector<double> &opac_c,
             whole = true;
         }
     }
+    // DELO-parabolic, whose bodies leave two waves per SIMD: four waves per block
+    // for any other single slab (200 points, 20 x 101 rays: operator 11.0 -> 10.2
+    // us, GMRES 759 -> 652 us; 400 points, 32 x 201: 13.8 -> 12.1, 2.05 -> 2.10 ms).
+    if (!opt.sweep_waves && h->fs == RT_FS_DELO_PARABOLIC && !whole) h->W = wpd = 4;
+    const long long dirs_total = (long long)h->n_atm * h->M;
+    long long batches_total = 0;
+    for (int n : h->ns) batches_total += (long long)h->M * slab_tiles(n, h->L, h->nc).nwb;
+    // Big batches: the fewest waves per direction (a power of two) that still
+    // give five waves per SIMD, so that what a wave does once -- sources,
+    // depth steps, the sum over its rays -- is shared by more of its ray
+    // batches.  FP64 / FP32 operator, slabs of 64 to 512 points, 16 directions,
+    // 101 frequencies, us with 4, 2 and 1 waves per direction: 256 slabs
+    // 65 / 35, 61 / 35, 85 / 50; 320 slabs 89 / 41, 85 / 39, 100 / 52; 512
+    // slabs 136 / 66, 126 / 59, 124 / 69; 1024 slabs 263 / 140, 242 / 124,
+    // 233 / 124.
+    if (opt.wave_batches == 0 && !whole)
+        while (wpd > 1 && dirs_total * (wpd / 2) >= 5 * 4 * 256) wpd /= 2;
     // Small ones: several blocks per direction, two waves per SIMD in all but
     // at least two batches per wave (below that a block's fixed part costs
     // more than the shorter chain saves).  With about 48 blocks in all
