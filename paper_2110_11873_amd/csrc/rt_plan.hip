@@ -259,9 +259,13 @@ int plan_sweeps(rt_handle *h, const rt_problem *p, std::vector<double> &opac_c,
     // 101 frequencies, us with 4, 2 and 1 waves per direction: 256 slabs
     // 65 / 35, 61 / 35, 85 / 50; 320 slabs 89 / 41, 85 / 39, 100 / 52; 512
     // slabs 136 / 66, 126 / 59, 124 / 69; 1024 slabs 263 / 140, 242 / 124,
-    // 233 / 124.
+    // 233 / 124.  Not where a block would then have places for twice the slab's
+    // directions or more, and half of its waves nothing to do (6000 slabs of 64 to
+    // 128 points, 2 directions of one |mu|, 51 frequencies: 57 us with four waves
+    // on it, 77 with one and three idle).
     if (opt.wave_batches == 0 && !whole)
-        while (wpd > 1 && dirs_total * (wpd / 2) >= 5 * 4 * 256) wpd /= 2;
+        while (wpd > 1 && dirs_total * (wpd / 2) >= 5 * 4 * 256 && h->W / (wpd / 2) < 2 * h->M)
+            wpd /= 2;
     // Small ones: several blocks per direction, two waves per SIMD in all but
     // at least two batches per wave (below that a block's fixed part costs
     // more than the shorter chain saves).  With about 48 blocks in all
