@@ -270,9 +270,15 @@ int plan_sweeps(rt_handle *h, const rt_problem *p, std::vector<double> &opac_c,
     // at least two batches per wave (below that a block's fixed part costs
     // more than the shorter chain saves).  With about 48 blocks in all
     // instead: one 1024-point slab 30.8 -> 24.6 us FP64, 21.6 -> 16.1 FP32; 8
-    // slabs 16.7 -> 10.4; 32 slabs 22.9 -> 17.7; 64 slabs 24.8 -> 23.0.
-    constexpr long long kFillWaves = 2 * 4 * 256;
-    const int nb_fill = (int)std::max<long long>(2, (batches_total + kFillWaves - 1) / kFillWaves);
+    // slabs 16.7 -> 10.4; 32 slabs 22.9 -> 17.7; 64 slabs 24.8 -> 23.0.  Bodies of
+    // chunks longer than 8 leave one FP64 wave per SIMD, so there one wave per SIMD
+    // in all, if the directions leave room for it: a second round of blocks of two
+    // batches takes as long as the first.  FP64 operator with two and one, us: one
+    // 1024-point slab of 32 x 201 distinct rays 42.6 and 28.0, 3 slabs of 1000
+    // points and 16 x 101 41.5 and 25.9, 8 slabs of 1024 points 48.8 and 34.6;
+    // but 40 slabs of 700, whose 320 directions do not fit one round, 58.7 and 67.8.
+    const long long fill_waves = (h->L > 8 && dirs_total <= 256 ? 1 : 2) * 4 * 256;
+    const int nb_fill = (int)std::max<long long>(2, (batches_total + fill_waves - 1) / fill_waves);
     // The plan that the Arnoldi step reads: at least kSolveWb batches per wave,
     // but two where a single slab then has no more than kOneXcd blocks.
     const int slab_blocks = h->M * ((slab_tiles(h->ns_max, h->L, h->nc).nwb + 2 * h->W - 1) / (2 * h->W));
