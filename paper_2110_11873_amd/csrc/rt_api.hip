@@ -287,8 +287,8 @@ int hip_check(hipError_t e, const char *what) {
 static SweepArgs sweep_args(rt_handle *h, const double *in, const double *scale, double *out,
                             const int *mask, bool fp32, int mode) {
     SweepArgs a{};
-    a.atm = plan_of(h).d_atm;
-    a.blk = plan_of(h).d_blk;
+    a.atm = plan_of(h, fp32).d_atm;
+    a.blk = plan_of(h, fp32).d_blk;
     const int cm = coef_mode_of(h, fp32);
     a.coef = cm == kCoefParabolic ? (const void *)h->d_coef64
              : cm == kCoefPairs ? (fp32 ? (const void *)h->d_coef32 : (const void *)h->d_coef64)
@@ -315,11 +315,11 @@ hipError_t apply_sweep(rt_handle *h, const double *in, const double *scale, cons
                        bool fp32, hipStream_t s) {
     fp32 = sweeps_fp32(h, fp32);
     SweepArgs a = sweep_args(h, in, scale, nullptr, mask, fp32, 0);
-    a.spread = plan_of(h).spread;
+    a.spread = plan_of(h, fp32).spread;
     int W;
     bool pf;
     sweep_config(h, fp32, &W, &pf);
-    return launch_sweep(h->L, W, pf, fp32, coef_mode_of(h, fp32), a, plan_of(h).n_blocks,
+    return launch_sweep(h->L, W, pf, fp32, coef_mode_of(h, fp32), a, plan_of(h, fp32).n_blocks,
                         h->ns_max, s);
 }
 
@@ -330,25 +330,25 @@ hipError_t apply_operator_into(rt_handle *h, const double *in, double *out, doub
     int W;
     bool pf;
     sweep_config(h, false, &W, &pf);
-    a.whole = plan_of(h).whole ? 1 : 0;
+    a.whole = plan_of(h, false).whole ? 1 : 0;
     hipError_t e = launch_sweep(h->L, W, pf, false, coef_mode_of(h, false), a,
-                                plan_of(h).n_blocks, h->ns_max, s);
+                                plan_of(h, false).n_blocks, h->ns_max, s);
     if (e != hipSuccess || a.whole) return e;
-    return launch_finalize(a, h->n_atm, h->ns_max, plan_of(h).nblk_max, s);
+    return launch_finalize(a, h->n_atm, h->ns_max, plan_of(h, false).nblk_max, s);
 }
 
 hipError_t apply_operator(rt_handle *h, const double *in, const double *scale, double *out,
                           const int *mask, bool fp32, int mode, hipStream_t s) {
     fp32 = sweeps_fp32(h, fp32);
     SweepArgs a = sweep_args(h, in, scale, out, mask, fp32, mode);
-    a.whole = plan_of(h).whole ? 1 : 0;
+    a.whole = plan_of(h, fp32).whole ? 1 : 0;
     int W;
     bool pf;
     sweep_config(h, fp32, &W, &pf);
-    hipError_t e = launch_sweep(h->L, W, pf, fp32, coef_mode_of(h, fp32), a, plan_of(h).n_blocks,
+    hipError_t e = launch_sweep(h->L, W, pf, fp32, coef_mode_of(h, fp32), a, plan_of(h, fp32).n_blocks,
                                 h->ns_max, s);
     if (e != hipSuccess || a.whole) return e;
-    return launch_finalize(a, h->n_atm, h->ns_max, plan_of(h).nblk_max, s);
+    return launch_finalize(a, h->n_atm, h->ns_max, plan_of(h, fp32).nblk_max, s);
 }
 
 void clear_graphs(rt_handle *h) {
@@ -594,7 +594,7 @@ int rt_setup(rt_handle **out, const rt_problem *p, const rt_options *o) {
         put(&h->d_opac_c, opac_c.data(), nmerged);
         put(&h->d_wphi_c, wphi_c.data(), nmerged);
         put(&h->d_pt_atm, pt_atm.data(), acc);
-        for (SweepPlan *pl : {&h->main, &h->tail}) {
+        for (SweepPlan *pl : {&h->main, &h->main32, &h->tail}) {
             if (!pl->n_blocks) continue;
             put(&pl->d_atm, pl->atm.data(), pl->atm.size());
             put(&pl->d_blk, pl->blk.data(), pl->blk.size());

@@ -274,10 +274,11 @@ struct rt_handle {
     int L = 8;                 // chunk length the tiles were built for
     int W = 4;                 // waves per sweep block the plan was made for
     long long n_pairs = 0, n_partial = 0;
-    // the main plan, and the tail plan over the same coefficient tiles (none when
-    // it would equal the main plan); plan_tail selects it for the sweeps, their
-    // finalize pass and the fused Arnoldi step
-    rt::SweepPlan main, tail;
+    // the main plan, that of the FP32 sweeps and the tail plan over the same
+    // coefficient tiles (none where it would equal the main plan); plan_tail
+    // selects the tail plan for the sweeps, their finalize pass and the fused
+    // Arnoldi step
+    rt::SweepPlan main, main32, tail;
     bool plan_tail = false;
 
     // device copies of the problem
@@ -378,12 +379,15 @@ struct rt_handle {
 
 namespace rt {
 
-// The plan the sweeps use now.
-inline const SweepPlan &plan_of(const rt_handle *h) { return h->plan_tail ? h->tail : h->main; }
+// The plan the sweeps asked for in FP64 or FP32 use now.
+inline const SweepPlan &plan_of(const rt_handle *h, bool fp32) {
+    if (h->plan_tail) return h->tail;
+    return h->main32.n_blocks && sweeps_fp32(h, fp32) ? h->main32 : h->main;
+}
 // Whether a sweep asked for in FP32 leaves its partial sums in FP32: where a block
 // has one direction (FP64 where it adds several).
 inline bool partial_fp32(const rt_handle *h, bool fp32) {
-    return sweeps_fp32(h, fp32) && plan_of(h).wpd == h->W;
+    return sweeps_fp32(h, fp32) && plan_of(h, fp32).wpd == h->W;
 }
 
 // sigma_out = A (scale .* sigma_in) for the slabs whose mask is set (all if

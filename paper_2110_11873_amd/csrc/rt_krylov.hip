@@ -1436,7 +1436,7 @@ struct Driver {
             // the tail plan; the choice is made here only, so eager launches
             // and graph replays take the same plan in every cycle
             h->plan_tail = h->tail.n_blocks > 0 && act <= kTailSlabs;
-            a.atm = plan_of(h).d_atm;
+            a.atm = plan_of(h, fp32).d_atm;
             key.back() = h->plan_tail ? 1 : 0;
             if (h->opt.graphs) {
                 graph(key, [&]() {

@@ -266,6 +266,15 @@ int plan_sweeps(rt_handle *h, const rt_problem *p, std::vector<double> &opac_c,
     if (opt.wave_batches == 0 && !whole)
         while (wpd > 1 && dirs_total * (wpd / 2) >= 5 * 4 * 256 && h->W / (wpd / 2) < 2 * h->M)
             wpd /= 2;
+    // FP32 sweeps: no wave adds up more ray batches in FP32 than it would with a
+    // ray per frequency and every wave of a block on one direction (512 and 1024
+    // slabs of distinct opacities, errors against the FP64 operator 2.04e-7 and
+    // 1.51e-7 normwise with the waves per direction above, 1.93e-7 and 1.34e-7 so).
+    int wpd32 = wpd;
+    for (int n : h->ns) {
+        const int now = slab_tiles(n, h->L, h->nc).nwb, all = slab_tiles(n, h->L, h->n_nu).nwb;
+        while (!whole && wpd32 < h->W && (now + wpd32 - 1) / wpd32 > (all + h->W - 1) / h->W) wpd32 *= 2;
+    }
     // Small ones: several blocks per direction, two waves per SIMD in all but
     // at least two batches per wave (below that a block's fixed part costs
     // more than the shorter chain saves).  With about 48 blocks in all
@@ -284,7 +293,7 @@ int plan_sweeps(rt_handle *h, const rt_problem *p, std::vector<double> &opac_c,
     const int slab_blocks = h->M * ((slab_tiles(h->ns_max, h->L, h->nc).nwb + 2 * h->W - 1) / (2 * h->W));
     const int solve_wb = h->n_atm == 1 && slab_blocks <= kOneXcd ? 2 : kSolveWb;
     std::vector<AtmDesc> atm(h->n_atm);
-    std::vector<int> nb(h->n_atm), nb_tail(h->n_atm);
+    std::vector<int> nb(h->n_atm), nb32(h->n_atm), nb_tail(h->n_atm);
     for (int a = 0; a < h->n_atm; ++a) {
         AtmDesc &d = atm[a];
         d.ns = h->ns[a];
@@ -313,11 +322,13 @@ int plan_sweeps(rt_handle *h, const rt_problem *p, std::vector<double> &opac_c,
         nb[a] = std::min(std::min(nb_fill, 32), (d.nwb + wpd - 1) / wpd);
         if (wpd < h->W || whole) nb[a] = (d.nwb + wpd - 1) / wpd;
         if (opt.wave_batches > 0) nb[a] = opt.wave_batches;
+        nb32[a] = std::min((d.nwb + wpd32 - 1) / wpd32, 32);
         // a plan the caller fixed is kept for every cycle
         nb_tail[a] = opt.wave_batches > 0 ? nb[a] : std::min(std::max(nb[a], solve_wb), kTailWb);
     }
     h->main = make_plan(atm, h->M, h->W, wpd, nb);
     h->main.whole = whole;
+    if (wpd32 != wpd && sweeps_fp32(h, true)) h->main32 = make_plan(atm, h->M, h->W, wpd32, nb32);
     // the tail plan, over the same tiles, only where it differs
     SweepPlan tail = make_plan(atm, h->M, h->W, h->W, nb_tail);
     if (tail.n_blocks != h->main.n_blocks) h->tail = std::move(tail);
@@ -332,7 +343,7 @@ int plan_sweeps(rt_handle *h, const rt_problem *p, std::vector<double> &opac_c,
     SweepPlan &solve = h->tail.n_blocks ? h->tail : h->main;
     if (h->n_atm == 1 && solve.n_blocks > 1 && solve.n_blocks <= kOneXcd && h->ns_max <= 512)
         solve.spread = 3;
-    h->n_partial = std::max(h->main.n_partial, h->tail.n_partial);
+    h->n_partial = std::max({h->main.n_partial, h->main32.n_partial, h->tail.n_partial});
     return RT_OK;
 }
 

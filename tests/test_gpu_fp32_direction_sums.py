@@ -34,3 +34,18 @@ def test_directions_are_added_in_fp64(n, ns, deep):
         err = (h.apply_op_fp32(u) - h.apply_op(u))[0::2].abs().cpu().numpy()
     # sources up to 8, four terms of each direction; the deep slab only sets the block's LDS
     assert err[deep:].max() <= 8 * 4 * small * 1e-6
+
+
+@pytest.mark.parametrize("n,m,n_nu,ns", [(1300, 4, 41, 30), (2700, 2, 23, 80), (700, 8, 9, 20)])
+def test_waves_add_no_more_batches_in_fp32_than_with_a_ray_per_frequency(n, m, n_nu, ns):
+    """Where no opacities are equal: the same sums, to the bit, as with all four
+    waves of a block on one direction (a fixed number of batches per wave)."""
+    p = W.make_slabs([ns] * n, [(1e-3, 1e4)] * n, 2 * m, n_nu, 4.0, [1e-3] * n, [1e-2] * n, [0.5] * n)
+    p = p.with_(opac=p.opac * (1 + 1e-3 * np.arange(n_nu)))
+    u = torch.from_numpy(W.random_vector(p.n_unknowns, n)).cuda()
+    with B.setup(p) as h:
+        y = h.apply_op_fp32(u)
+        x = h.apply_op(u)
+    with B.setup(p, wave_batches=32) as h:
+        assert torch.equal(h.apply_op_fp32(u), y)
+        assert (h.apply_op(u) - x).abs().max() <= 1e-12 * (u.abs().max() + (x - u).abs().max())
