@@ -623,7 +623,7 @@ __device__ __forceinline__ void sweep_rays(const SweepArgs &a, const BlockDesc &
     const double2 tf = a.dirc[m];
     const T t1 = (T)tf.x, t12 = (T)tf.y;
 
-    // block totals of the 2 ns quadrature sums.  A direction's sum over its waves
+    // block totals of the 2 ns quadrature sums.  The sum over a direction's waves
     // is taken and stored in the sweep's type (an FP32 sweep's sums are FP32
     // values: half the bytes, the same numbers); directions are added in FP64, by
     // the finalize pass or, where a block has several, here.
@@ -649,30 +649,38 @@ __device__ __forceinline__ void sweep_rays(const SweepArgs &a, const BlockDesc &
             }
         }
         __syncthreads();
-        auto total = [&](int e) {
-            double s = 0.0;
-            T d = (T)0;
-            for (int w = 0; w < W; ++w) {
-                d += sacc[(long long)w * 2 * ns + e];
-                if (sizeof(T) == 4 && ((w + 1) & (wpd - 1)) == 0) {  // a direction is complete
-                    s += (double)d;
-                    d = (T)0;
-                }
-            }
-            return sizeof(T) == 4 ? s : (double)d;
-        };
         if constexpr (LE <= 4) {  // plans of chunk length 4 only: longer bodies keep their registers
             if (a.whole) {  // this block has all of the slab's rays
-                for (int k = threadIdx.x; k < ns; k += nthr)
-                    finalize_point(a, bd.atm, at, k, total(2 * k), total(2 * k + 1));
+                for (int k = threadIdx.x; k < ns; k += nthr) {
+                    double j0 = (double)sacc[2 * k], j2 = (double)sacc[2 * k + 1];
+                    for (int w = 1; w < W; ++w) {
+                        j0 += (double)sacc[(long long)w * 2 * ns + 2 * k];
+                        j2 += (double)sacc[(long long)w * 2 * ns + 2 * k + 1];
+                    }
+                    finalize_point(a, bd.atm, at, k, j0, j2);
+                }
                 return;
             }
         }
+        if (wide) {
+            for (int e = threadIdx.x; e < 2 * ns; e += nthr) {
+                double s = 0.0;
+                T d = (T)0;
+                for (int w = 0; w < W; ++w) {
+                    d += sacc[(long long)w * 2 * ns + e];
+                    if (((w + 1) & (wpd - 1)) == 0) {  // a direction is complete
+                        s += (double)d;
+                        d = (T)0;
+                    }
+                }
+                mine64[e] = s;
+            }
+            return;
+        }
         for (int e = threadIdx.x; e < 2 * ns; e += nthr) {
-            if (wide)
-                mine64[e] = total(e);
-            else
-                mine[e] = (T)total(e);
+            T s = sacc[e];
+            for (int w = 1; w < W; ++w) s += sacc[(long long)w * 2 * ns + e];
+            mine[e] = s;
         }
     } else {
         // one shared row, filled wave after wave (fixed order)
