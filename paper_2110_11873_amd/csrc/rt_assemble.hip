@@ -532,8 +532,9 @@ int plan_assembly(rt_handle *h, hipStream_t s) {
     });
     h->asm_tasks = (int)tasks.size();
     int rc;
-    // the task list is set on the handle last: it marks the plan as made, so
-    // a failure frees whatever this call allocated and a later call starts over
+    // the task list is set on the handle last, after the tables' launches: it
+    // marks the plan as made, so a failure frees whatever this call allocated and
+    // a later call starts over
     AsmTask *dt = nullptr;
     auto undo = [&](int code) {
         for (void **q : {(void **)&dt, (void **)&h->d_ew, (void **)&h->d_asm_dg,
@@ -568,17 +569,19 @@ int plan_assembly(rt_handle *h, hipStream_t s) {
         return undo(fail(RT_EDEVICE, "assembly tile table upload failed"));
     if ((rc = alloc(&h->d_asm_xt, slots * kTile)) != RT_OK) return undo(rc);
     if ((rc = alloc(&h->d_asm_tt, slots)) != RT_OK) return undo(rc);
-    h->d_asm_task = dt;
     int ns_max_m1 = 1;
     for (int n : h->ns) ns_max_m1 = std::max(ns_max_m1, n - 1);
     const long long per = (long long)ns_max_m1 * h->M * h->nc;
     const dim3 grid((unsigned)std::min<long long>((per + 255) / 256, 4096), h->n_atm);
     hipLaunchKernelGGL(ew_table_kernel, grid, dim3(256), 0, s, h->d_atm, h->d_tau, h->d_opac_c,
                        h->d_mu_pos, h->M, h->nc, h->fs, h->d_ew);
-    if (hipGetLastError() != hipSuccess) return fail(RT_EDEVICE, "assembly coefficient launch failed");
+    if (hipGetLastError() != hipSuccess)
+        return undo(fail(RT_EDEVICE, "assembly coefficient launch failed"));
     hipLaunchKernelGGL(tile_table_kernel, dim3(2 * ((ns_max_m1 + kTile) / kTile), h->n_atm), dim3(256),
                        0, s, asm_args(h), h->d_asm_xt, h->d_asm_tt);
-    if (hipGetLastError() != hipSuccess) return fail(RT_EDEVICE, "assembly tile table launch failed");
+    if (hipGetLastError() != hipSuccess)
+        return undo(fail(RT_EDEVICE, "assembly tile table launch failed"));
+    h->d_asm_task = dt;
     return RT_OK;
 }
 

@@ -816,15 +816,19 @@ int prd_table(rt_handle *h) {
         return RT_OK;
     choose_prd_sweep(h);
     if (!h->prd_cached_nt) return RT_OK;
-    if (hipMalloc((void **)&h->d_prd_cuk, sizeof(double2) * rows) != hipSuccess) {
-        h->d_prd_cuk = nullptr;
+    double2 *cuk = nullptr;
+    if (hipMalloc((void **)&cuk, sizeof(double2) * rows) != hipSuccess) {
         (void)hipGetLastError();
         return RT_OK;
     }
     hipLaunchKernelGGL(prd_cuk_kernel, dim3(h->n_nu, h->n_atm), dim3(256), 0, nullptr,
-                       prd_args(h, nullptr, nullptr), reinterpret_cast<double2 *>(h->d_prd_cuk));
-    if (hipGetLastError() != hipSuccess || hipStreamSynchronize(nullptr) != hipSuccess)
+                       prd_args(h, nullptr, nullptr), cuk);
+    if (hipGetLastError() != hipSuccess || hipStreamSynchronize(nullptr) != hipSuccess) {
+        (void)hipGetLastError();
+        (void)hipFree(cuk);
         return fail(RT_EDEVICE, "redistribution coefficient table");
+    }
+    h->d_prd_cuk = reinterpret_cast<double *>(cuk);  // filled: a failed one is not kept
     return RT_OK;
 }
 
