@@ -56,7 +56,8 @@ struct AsmArgs {
     const AsmTask *task;
     const double2 *ew;       // (E, w) per slab, interval and ray
     const double *xt, *tt;   // tile transmissions: tile_table_kernel
-    const long long *tile0;  // per slab: tiles of the slabs before it
+    const long long *tile0;  // per slab: tiles of the slabs before it in its group
+    int slab0;               // tile_table_kernel: the group's first slab
     const RayConst *rayc;
     const double2 *dirc;     // per |mu|: (T1, T1^2 + T2^2)
     double *A;               // final A, or the raw moments of slice 0
@@ -108,12 +109,13 @@ __device__ inline int ew_row(int dir, int k, int ns) { return dir == 0 ? k - 1 :
 // the chunk, so a wavefront reads step i of its A operand -- 16 rows of the
 // four rays that its four lane groups hold -- as 64 consecutive entries.
 __global__ void tile_table_kernel(AsmArgs g, double *xt, double *tt) {
-    const AtmDesc at = g.atm[blockIdx.y];
+    const int slab = g.slab0 + blockIdx.y;
+    const AtmDesc at = g.atm[slab];
     const int ns = at.ns, nt = (ns + kTile - 1) / kTile;
     if ((int)blockIdx.x >= 2 * nt) return;
     const int dir = blockIdx.x / nt, b = (blockIdx.x % nt) * kTile;
     const int nchunks = g.M * g.cpm, R = g.M * g.n_nu, RI = g.rg / 4;
-    const long long tile = 2 * g.tile0[blockIdx.y] + blockIdx.x;
+    const long long tile = 2 * g.tile0[slab] + blockIdx.x;
     // the products of 256 rays at a time in LDS (rays in the order of the (E, w)
     // table, then slots in the order of the output)
     __shared__ double Xs[256 * (kTile + 1)];
@@ -495,9 +497,27 @@ AsmArgs asm_args(const rt_handle *h) {
     return g;
 }
 
+// The tile transmissions of one group of slabs.
+int fill_tables(const rt_handle *h, const rt_handle::AsmGroup &gr, hipStream_t s) {
+    AsmArgs g = asm_args(h);
+    g.slab0 = gr.slab0;
+    int ns_max = 1;
+    for (int a = gr.slab0; a < gr.slab1; ++a) ns_max = std::max(ns_max, h->ns[a]);
+    hipLaunchKernelGGL(tile_table_kernel, dim3(2 * ((ns_max + kTile - 1) / kTile), gr.slab1 - gr.slab0),
+                       dim3(256), 0, s, g, h->d_asm_xt, h->d_asm_tt);
+    if (hipGetLastError() != hipSuccess) return fail(RT_EDEVICE, "assembly tile table launch failed");
+    return RT_OK;
+}
+
 // Plan the assembly once per handle: frequency groups of RG rays per
 // wavefront (the fewest slices, then the smallest RG), wavefronts per
 // workgroup, the task list (longest walks first) and the workspace.
+//
+// The tile transmissions take as much memory again as the (E, w) table (17 bytes
+// per depth and ray slot; 512 slabs of 64 to 512 points, 8 |mu| x 51 distinct
+// opacities: 1.1 GB, kept on the handle).  Where there is no room for all of them, the
+// slabs are assembled in groups that share the memory of the largest group, whose
+// tables are then made in every call.
 int plan_assembly(rt_handle *h, hipStream_t s) {
     if (h->d_asm_task) return RT_OK;
     // the fewest slices, then the fewest empty ray slots, then the smaller variant
@@ -520,17 +540,38 @@ int plan_assembly(rt_handle *h, hipStream_t s) {
     h->asm_cpm = (h->nc + best_rg - 1) / best_rg;
     h->asm_slices = best_slices;
     h->asm_nw = best_nw;
+    // groups of consecutive slabs of about tiles / n tiles each
+    long long tiles = 0;
+    for (int n : h->ns) tiles += (n + kTile - 1) / kTile;
+    std::vector<long long> tile0(h->n_atm);
     std::vector<AsmTask> tasks;
-    for (int a = 0; a < h->n_atm; ++a)
-        for (int d = 0; d < 2; ++d)
-            for (int jb = 0; jb * kWave < h->ns[a]; ++jb)
-                for (int sl = 0; sl < best_slices; ++sl) tasks.push_back(AsmTask{a, d, jb, sl});
-    // longest walks first.  (A slab's tasks, which read the same tile table, on
-    // one XCD measured 2.50 ms against 2.39 for 512 slabs.)
-    std::stable_sort(tasks.begin(), tasks.end(), [&](const AsmTask &x, const AsmTask &y) {
-        return h->ns[x.atm] - kWave * x.jblk > h->ns[y.atm] - kWave * y.jblk;
-    });
-    h->asm_tasks = (int)tasks.size();
+    long long most = 0;  // tiles of the largest group
+    auto split = [&](int n) {
+        h->asm_groups.clear();
+        tasks.clear();
+        most = 0;
+        for (int a = 0; a < h->n_atm;) {
+            rt_handle::AsmGroup gr{a, a, (int)tasks.size(), 0};
+            long long t = 0;
+            for (; gr.slab1 < h->n_atm && (t == 0 || t < (tiles + n - 1) / n); ++gr.slab1) {
+                tile0[gr.slab1] = t;
+                t += (h->ns[gr.slab1] + kTile - 1) / kTile;
+            }
+            for (; a < gr.slab1; ++a)
+                for (int d = 0; d < 2; ++d)
+                    for (int jb = 0; jb * kWave < h->ns[a]; ++jb)
+                        for (int sl = 0; sl < best_slices; ++sl) tasks.push_back(AsmTask{a, d, jb, sl});
+            gr.tasks = (int)tasks.size() - gr.task0;
+            // longest walks first.  (A slab's tasks, which read the same tile table, on
+            // one XCD measured 2.50 ms against 2.39 for 512 slabs.)
+            std::stable_sort(tasks.begin() + gr.task0, tasks.end(),
+                             [&](const AsmTask &x, const AsmTask &y) {
+                                 return h->ns[x.atm] - kWave * x.jblk > h->ns[y.atm] - kWave * y.jblk;
+                             });
+            most = std::max(most, t);
+            h->asm_groups.push_back(gr);
+        }
+    };
     int rc;
     // the task list is set on the handle last, after the tables' launches: it
     // marks the plan as made, so a failure frees whatever this call allocated and
@@ -545,30 +586,32 @@ int plan_assembly(rt_handle *h, hipStream_t s) {
         }
         return code;
     };
-    if ((rc = alloc(&dt, tasks.size())) != RT_OK) return undo(rc);
-    if (hipMemcpy(dt, tasks.data(), tasks.size() * sizeof(AsmTask), hipMemcpyHostToDevice) !=
-        hipSuccess)
-        return undo(fail(RT_EDEVICE, "assembly task upload failed"));
     if ((rc = alloc(&h->d_ew, (size_t)h->n_ew)) != RT_OK) return undo(rc);
     if ((rc = alloc(&h->d_asm_dg, (size_t)best_slices * 2 * h->ns_total * 3)) != RT_OK)
         return undo(rc);
     if (best_slices > 1 &&
         (rc = alloc(&h->d_asm_sc, (size_t)(best_slices - 1) * h->n_dense)) != RT_OK)
         return undo(rc);
-    // the tile transmissions
-    std::vector<long long> tile0(h->n_atm);
-    long long tiles = 0;
-    for (int a = 0; a < h->n_atm; ++a) {
-        tile0[a] = tiles;
-        tiles += (h->ns[a] + kTile - 1) / kTile;
-    }
-    const size_t slots = (size_t)2 * tiles * h->M * h->asm_cpm * best_rg;
+    split(1);
+    if ((rc = alloc(&dt, tasks.size())) != RT_OK) return undo(rc);
     if ((rc = alloc(&h->d_asm_tile0, tile0.size())) != RT_OK) return undo(rc);
+    // the tile transmissions, of as few groups as there is room for
+    for (int n = 2;; n *= 2) {
+        const size_t slots = (size_t)2 * most * h->M * h->asm_cpm * best_rg;
+        if ((rc = alloc(&h->d_asm_xt, slots * kTile)) == RT_OK &&
+            (rc = alloc(&h->d_asm_tt, slots)) == RT_OK)
+            break;
+        if (h->d_asm_xt) (void)hipFree(h->d_asm_xt);
+        h->d_asm_xt = nullptr;
+        if ((int)h->asm_groups.size() == h->n_atm) return undo(rc);
+        split(n);
+    }
+    if (hipMemcpy(dt, tasks.data(), tasks.size() * sizeof(AsmTask), hipMemcpyHostToDevice) !=
+        hipSuccess)
+        return undo(fail(RT_EDEVICE, "assembly task upload failed"));
     if (hipMemcpy(h->d_asm_tile0, tile0.data(), tile0.size() * sizeof(long long),
                   hipMemcpyHostToDevice) != hipSuccess)
         return undo(fail(RT_EDEVICE, "assembly tile table upload failed"));
-    if ((rc = alloc(&h->d_asm_xt, slots * kTile)) != RT_OK) return undo(rc);
-    if ((rc = alloc(&h->d_asm_tt, slots)) != RT_OK) return undo(rc);
     int ns_max_m1 = 1;
     for (int n : h->ns) ns_max_m1 = std::max(ns_max_m1, n - 1);
     const long long per = (long long)ns_max_m1 * h->M * h->nc;
@@ -577,10 +620,8 @@ int plan_assembly(rt_handle *h, hipStream_t s) {
                        h->d_mu_pos, h->M, h->nc, h->fs, h->d_ew);
     if (hipGetLastError() != hipSuccess)
         return undo(fail(RT_EDEVICE, "assembly coefficient launch failed"));
-    hipLaunchKernelGGL(tile_table_kernel, dim3(2 * ((ns_max_m1 + kTile) / kTile), h->n_atm), dim3(256),
-                       0, s, asm_args(h), h->d_asm_xt, h->d_asm_tt);
-    if (hipGetLastError() != hipSuccess)
-        return undo(fail(RT_EDEVICE, "assembly tile table launch failed"));
+    if (h->asm_groups.size() == 1 && (rc = fill_tables(h, h->asm_groups[0], s)) != RT_OK)
+        return undo(rc);
     h->d_asm_task = dt;
     return RT_OK;
 }
@@ -592,8 +633,13 @@ int assemble(rt_handle *h, double *A, hipStream_t s) {
     if (rc != RT_OK) return rc;
     AsmArgs g = asm_args(h);
     g.A = A;
-    if (launch_assemble(g, h->asm_tasks, s) != hipSuccess)
-        return fail(RT_EDEVICE, "assembly launch failed");
+    const AsmTask *tasks = g.task;
+    for (const rt_handle::AsmGroup &gr : h->asm_groups) {
+        if (h->asm_groups.size() > 1 && (rc = fill_tables(h, gr, s)) != RT_OK) return rc;
+        g.task = tasks + gr.task0;
+        if (launch_assemble(g, gr.tasks, s) != hipSuccess)
+            return fail(RT_EDEVICE, "assembly launch failed");
+    }
     if (g.slices > 1) {
         long long nsq = 1;
         for (int n : h->ns) nsq = std::max(nsq, (long long)n * n);

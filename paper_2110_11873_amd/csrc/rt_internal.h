@@ -328,11 +328,15 @@ struct rt_handle {
     // dense route (allocated on first use)
     double2 *d_ew = nullptr;      // (E, w) per slab, interval and ray
     double *d_asm_xt = nullptr, *d_asm_tt = nullptr;  // transmissions within tiles of 16 depths
-    long long *d_asm_tile0 = nullptr;  // tiles of the slabs before each slab
+    long long *d_asm_tile0 = nullptr;  // tiles of the slabs before each slab in its group
     double *d_asm_dg = nullptr;   // node-diagonal moments per slice and direction
     double *d_asm_sc = nullptr;   // raw moments of ray slices after the first
     void *d_asm_task = nullptr;   // assembly task list
-    int asm_tasks = 0, asm_rg = 0, asm_nw = 0, asm_cpm = 0, asm_slices = 0;
+    int asm_rg = 0, asm_nw = 0, asm_cpm = 0, asm_slices = 0;
+    struct AsmGroup {
+        int slab0, slab1, task0, tasks;  // slabs slab0 .. slab1 - 1 and their tasks
+    };
+    std::vector<AsmGroup> asm_groups;  // one, unless the tables of all slabs found no room
     double *d_A = nullptr;        // the handle's assembled A (SOR, SSOR)
     bool dense_ready = false;
     double *d_pz = nullptr;       // P^-1 v for the triangular preconditioners
