@@ -90,7 +90,8 @@ int rt_sweep_coef_mode(const rt_handle *h, int fp32, int *mode);
  * hash of the sweep sources this library was built from.  rt_plan_key: the
  * key of problem p at precision (RT_PREC_*) on architecture arch (NULL: the
  * current device's, e.g. "gfx950"), written NUL-terminated into buf of
- * buflen bytes (RT_EINVAL if too short).  Host only.
+ * buflen bytes (RT_EINVAL if too short): of its shape and, unless the profiles
+ * are even, of the most distinct opacities of a slab.  Host only.
  */
 int rt_tuned_plan_status(const rt_handle *h);
 /* The options the handle runs with: the caller's, with the stored plan's

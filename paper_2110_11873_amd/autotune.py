@@ -14,7 +14,8 @@ full solve with the few fastest and keeps the plan whose solve is fastest:
 
 Plans are stored under the key the library computes for a problem
 (rt_plan_key: architecture, precision, formal solver, directions,
-frequencies, slabs, deepest slab, a hash of the depth counts), together with
+frequencies, slabs, deepest slab, a hash of the depth counts and, unless the
+profiles are even, the most distinct opacities of a slab), together with
 the hash of the sweep sources of the library that measured them.  Two files
 next to this module: tuned_plans.json holds every entry with its timing
 table; tuned_plans.txt, regenerated from it, is the one-line-per-plan index

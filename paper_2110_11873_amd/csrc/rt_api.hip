@@ -171,18 +171,23 @@ int validate(const rt_problem *p, const rt_options *o, std::vector<double> &mu_p
 // ---- stored launch plans (the autotuner's cache, read by rt_setup) --------
 // Key of a problem shape: architecture, precision, formal solver, directions,
 // frequencies, slabs, deepest slab and a 64-bit FNV-1a hash of the depth
-// counts -- the features the sweep's launch plan depends on.
+// counts and, where the profile is not even, of the number of distinct opacities
+// -- the features the sweep's launch plan depends on.
 std::string plan_key(const rt_problem *p, int precision, const std::string &arch) {
     unsigned long long f = 0xcbf29ce484222325ULL;
     int ns_max = 0;
-    for (int a = 0; a < p->n_atm; ++a) {
-        const unsigned int v = (unsigned int)p->ns[a];
+    auto add = [&](unsigned int v) {
         for (int b = 0; b < 4; ++b) {
             f ^= (v >> (8 * b)) & 0xffu;
             f *= 0x100000001b3ULL;
         }
+    };
+    for (int a = 0; a < p->n_atm; ++a) {
+        add((unsigned int)p->ns[a]);
         ns_max = std::max(ns_max, p->ns[a]);
     }
+    const int nc = distinct_opacities(p);
+    if (nc && nc != (p->n_nu + 1) / 2) add((unsigned int)nc);
     char hex[17];
     std::snprintf(hex, sizeof hex, "%016llx", f);
     std::ostringstream k;

@@ -209,6 +209,9 @@ hipError_t launch_diag(int npts, const int *pt_atm, const AtmDesc *atm, const do
                        const double *opac, const double *mu_pos, const RayConst *rayc, int M,
                        int n_nu, int fs, double *diag, double *dinv, hipStream_t s);
 bool sweep_chunk_supported(int L, bool fp32);
+// The most distinct opacities of a slab (rays per direction of the sweep); 0 for
+// opacities that rt_validate refuses.
+int distinct_opacities(const rt_problem *p);
 // The automatic chunk length, and the test that the tiles of a plan can be
 // addressed (rt_plan.hip).
 int auto_chunk(const std::vector<int> &ns, int rays);

@@ -2,6 +2,7 @@
 // chunks and wave-batches, the tile-ordered coefficients' layout, and the block
 // lists of the sweeps.
 #include <algorithm>
+#include <cmath>
 #include <string>
 #include <utility>
 #include <vector>
@@ -58,6 +59,7 @@ SlabTiles slab_tiles(int ns, int L, int n_nu) {
 // Strongest opacity first; every slab gets the same number of rays (the largest
 // count), the rest with weight zero.
 constexpr double kSameOpac = 1e-12;
+bool same_opacity(double first, double x) { return x - first <= kSameOpac * first; }
 
 int merge_frequencies(const rt_problem *p, std::vector<double> &opac, std::vector<double> &wphi) {
     const int n = p->n_nu;
@@ -73,7 +75,7 @@ int merge_frequencies(const rt_problem *p, std::vector<double> &opac, std::vecto
         for (int i = 0; i < n; ++g) {
             const double first = f[i].first;
             double sw = 0.0, excess = 0.0;  // of the opacity over the first's
-            for (; i < n && f[i].first - first <= kSameOpac * first; ++i) {
+            for (; i < n && same_opacity(first, f[i].first); ++i) {
                 sw += f[i].second;
                 excess += f[i].second * (f[i].first - first);
             }
@@ -165,6 +167,25 @@ SweepPlan make_plan(const std::vector<AtmDesc> &atm, int M, int W, int wpd,
 }
 
 }  // namespace
+
+int distinct_opacities(const rt_problem *p) {
+    if (!p->opac || p->n_nu < 1) return 0;
+    int most = 0;
+    std::vector<double> f(p->n_nu);
+    for (int a = 0; a < p->n_atm; ++a) {
+        std::copy_n(p->opac + (long long)a * p->n_nu, p->n_nu, f.begin());
+        for (double x : f)
+            if (!std::isfinite(x) || !(x > 0.0)) return 0;
+        std::sort(f.begin(), f.end());
+        int g = 0;
+        for (size_t i = 0; i < f.size(); ++g) {
+            const double first = f[i];
+            while (i < f.size() && same_opacity(first, f[i])) ++i;
+        }
+        most = std::max(most, g);
+    }
+    return most;
+}
 
 // Chunk length: the largest L whose lane count fills the chip (about two
 // waves per SIMD) -- longer chunks mean fewer scan steps and partial sums --
