@@ -59,8 +59,8 @@ extern "C" {
  * the upwind, current and downwind points of the ray, integrated exactly; the
  * last point of a ray takes the DELO-linear step.  Without dichroism, as
  * here, DELOPAR is the same step.  Its operator sweeps in FP64 (also in
- * RT_PREC_MIXED), with streamed coefficients of its own (rt_options.coef_mode
- * does not matter); rt_assemble, rt_solve_lu and the SOR/SSOR
+ * RT_PREC_MIXED), with streamed coefficients of its own, 16 bytes per ray and
+ * depth interval (rt_options.coef_mode does not matter); rt_assemble, rt_solve_lu and the SOR/SSOR
  * preconditioners are not available for it (RT_EINVAL). */
 #define RT_FS_DELO_PARABOLIC 3
 

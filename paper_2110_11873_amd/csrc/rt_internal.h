@@ -19,8 +19,9 @@ constexpr int kKrylovThreads = 256;
 constexpr int kKrylovEPT = (2 * RT_MAX_NS + kKrylovThreads - 1) / kKrylovThreads;
 
 // Per-slab launch plan of the formal-solver sweep.  A ray is one (|mu_m|, nu_p)
-// pair, nu_p standing for all frequencies of equal opacity ratio; its depth recurrence is split into C chunks, one chunk per lane,
-// G = 64 / C rays per wavefront ("wave-batch").  The first nlong chunks have
+// pair, nu_p standing for all frequencies of equal opacity ratio; its depth
+// recurrence is split into C chunks, one chunk per lane, G = 64 / C rays per
+// wavefront ("wave-batch").  The first nlong chunks have
 // Leff intervals, the others Leff - 1: a short chunk's last step is a
 // zero-length interval (the identity), which is neither stored nor loaded.
 // Wave-batches never mix directions: batch b of direction m holds the rays
@@ -52,8 +53,8 @@ struct AtmDesc {
 
 // One sweep block: directions m, m + 1, ... of slab atm, wpd waves each; wave w
 // handles wave-batches wb_first + w % wpd + t * wpd, t = 0, 1, ..., while below
-// wb_first + wb_count, of direction m + w / wpd.  The block writes its quadrature sums to partial-sum slot
-// `slot` of the slab.  The block list is ordered by decreasing work, so the
+// wb_first + wb_count, of direction m + w / wpd.  The block writes its quadrature
+// sums to partial-sum slot `slot` of the slab.  The block list is ordered by decreasing work, so the
 // in-order dispatch of workgroups starts the longest ones first.
 struct BlockDesc {
     int atm;

@@ -119,8 +119,9 @@ __global__ void ray_setup_kernel(const double *mu_pos, const double *w_pos, int 
 // only for the chunks that have one.  An entry is the pair (E, w) or w alone
 // (the sweep then derives E = 1 - w d).  Padding (frequencies beyond the
 // last, intervals beyond ns - 2) is E = w = 1 (DELO-parabolic, whose entries
-// are parabolic_pack's pairs: 1, -0): the step leaves I unchanged, and the source beyond the slab is zero.  The rays' quadrature weights and
-// (kappa, 1 / kappa) are laid out by slot (q_off + (m*nwb + b)*G + slot),
+// are parabolic_pack's pairs: 1, -0): the step leaves I unchanged, and the source
+// beyond the slab is zero.  The rays' quadrature weights and (kappa, 1 / kappa)
+// are laid out by slot (q_off + (m*nwb + b)*G + slot),
 // zero for padding rays, so the sweep never masks a loaded value.
 // --------------------------------------------------------------------------
 __global__ void coef_build_kernel(int M, const AtmDesc *atm, const BlockDesc *blk,
